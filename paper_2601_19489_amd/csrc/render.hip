@@ -2,8 +2,8 @@
 //
 // Forward: one workgroup per tile; each lane owns PX pixels. The tile's
 // sorted splat records are gathered through `vals` into LDS in batches;
-// every pixel walks the batch front to back. The workgroup stops as soon as
-// every pixel has reached T < 1e-4.
+// every wavefront walks the batch's splats that reach its pixels front to
+// back. The workgroup stops as soon as every pixel has reached T < 1e-4.
 //
 // Backward: one workgroup per tile, PX pixels per lane, walking the tile's
 // list back to front from each pixel's last contributor. The transmittance
@@ -51,13 +51,80 @@ __device__ __forceinline__ SplatQ eval_q(float px, float py, float u, float v, f
   return r;
 }
 
-__device__ __attribute__((noinline)) bool splat_skips_exact(float t, float px, float py, float u,
-                                                            float v, float a, float b, float c) {
+// q > t in FP64, the definition of the skip decision.
+__device__ __forceinline__ bool skips_f64(float t, float px, float py, float u, float v, float a,
+                                          float b, float c) {
 #pragma clang fp contract(off)
   const double dx = (double)px - (double)u;
   const double dy = (double)py - (double)v;
   const double q = dx * ((double)a * dx + 2.0 * ((double)b * dy)) + dy * ((double)c * dy);
   return q > (double)t;
+}
+
+__device__ __attribute__((noinline)) bool splat_skips_exact(float t, float px, float py, float u,
+                                                            float v, float a, float b, float c) {
+  return skips_f64(t, px, py, u, v, a, b, c);
+}
+
+// Which cells of a tile a splat can blend in. A cell is a block of CW x CH
+// pixels, one per lane of a wavefront; the splat is left out of a cell when
+// Q > t at all of its pixel centres, so leaving it out changes nothing.
+//
+// The smallest Q over the cell's rectangle of pixel centres lies on one of
+// its edges that face the centroid (Q grows along every ray from it), and on
+// an edge at -b d / c (or / a) clamped to it, so
+// two evaluations of Q give it; any other point of the rectangle would give a
+// larger value, so an inexact minimiser errs by the square of its error. The
+// FP32 value is within 8 u (1 + r) / (1 - r) of the exact one, relatively
+// (the bound of skip_band, the minimiser and the rectangle's own rounding
+// included), and the band is 16 u (1 + r) / (1 - r) t: a value above
+// t + band means Q > t at every pixel centre of the cell. An infinite band
+// (degenerate and non-finite records) keeps every cell.
+//
+// What it saves: a splat of a trained scene covers a few pixels, so it blends
+// in 8 to 25% of its tile's pixels and reaches 1.7 to 2.5 of a 16-pixel tile's
+// four cells (measured at 123k to 1M Gaussians of about their spacing's size;
+// 3.8 on the surface scene).
+template <int CW, int CH>
+__device__ __forceinline__ bool cell_reached(float x0, float y0, float u, float v, float a,
+                                             float b2, float c, float kx, float ky, float lim) {
+#pragma clang fp contract(fast)
+  const float dx0 = x0 + 0.5f - u, dx1 = x0 + ((float)CW - 0.5f) - u;
+  const float dy0 = y0 + 0.5f - v, dy1 = y0 + ((float)CH - 0.5f) - v;
+  const float ex = __builtin_amdgcn_fmed3f(0.f, dx0, dx1);  // the facing edges
+  const float ey = __builtin_amdgcn_fmed3f(0.f, dy0, dy1);
+  const float y = __builtin_amdgcn_fmed3f(ky * ex, dy0, dy1);
+  const float x = __builtin_amdgcn_fmed3f(kx * ey, dx0, dx1);
+  const float q1 = fmaf(ex, fmaf(b2, y, a * ex), (c * y) * y);
+  const float q2 = fmaf(x, fmaf(b2, ey, a * x), (c * ey) * ey);
+  return !(fminf(q1, q2) > lim);
+}
+
+// Bit i: cell i of the tile at (x0, y0) is reached; X(i), Y(i) the cell's
+// pixel offsets in the tile.
+template <int CW, int CH, int NCELL, class CellX, class CellY>
+__device__ __forceinline__ uint32_t cells_reached(float x0, float y0, float4 r0, float c, float t,
+                                                  float band, CellX X, CellY Y) {
+  const float a = r0.z, b = r0.w;
+  const float ky = -b * __builtin_amdgcn_rcpf(c), kx = -b * __builtin_amdgcn_rcpf(a);
+  // centroids out of the range in which the squares below stay finite: every cell
+  const float lim = fabsf(r0.x) + fabsf(r0.y) < 1e15f ? t + band : __builtin_huge_valf();
+  const float b2 = b + b;
+  uint32_t m = 0;
+#pragma unroll
+  for (int i = 0; i < NCELL; ++i)
+    if (cell_reached<CW, CH>(x0 + (float)X(i), y0 + (float)Y(i), r0.x, r0.y, a, b2, c, kx, ky,
+                             lim))
+      m |= 1u << i;
+  return m;
+}
+
+// 2 x + (the lane's bit of m), one instruction.
+__device__ __forceinline__ uint32_t shift_in(uint32_t x, uint64_t m) {
+  uint32_t r;
+  uint64_t carry;
+  asm("v_addc_co_u32 %0, %1, %2, %2, %3" : "=v"(r), "=s"(carry) : "v"(x), "s"(m));
+  return r;
 }
 
 // One front-to-back step of the forward at one pixel: skip (alpha < 1/255,
@@ -78,11 +145,51 @@ __device__ __forceinline__ int fwd_step(float px, float py, float4 a0, float4 a1
 }
 
 constexpr int kFwdBatch = 256;  // splats per LDS batch in the forward (default)
-template <int NB>
+constexpr int kFwdGroup = 4;    // splats a wavefront evaluates together (fwd_tile)
+// A batch in LDS, and per wavefront the byte offsets (16 per entry) of the
+// batch's splats that reach its cells. Entry NB holds a splat that blends
+// nowhere: it fills up a wavefront's last group.
+template <int NB, int NTH>
 struct FwdLdsT {
-  float4 s0[NB], s1[NB], s2[NB];
+  float4 s0[NB + 1], s1[NB + 1], s2[NB + 1];  // (u, v, a, 2 b), (c, t - band, t + band, o), (r, g, b, z)
+  float t[NB + 1];
+  uint32_t cells[NB + 1];
+  alignas(16) uint32_t list[NTH / kWave][NB + kFwdGroup];
 };
-using FwdLds = FwdLdsT<kFwdBatch>;
+
+// The forward's cells: 8 x 8 pixels, one per lane (lane l at column l % 8 and
+// row l / 8), numbered along a Z curve over the tile; wavefront w holds cells
+// w PX .. w PX + PX - 1.
+struct FwdCells {
+  __host__ __device__ static constexpr int x(int i) { return 8 * ((i & 1) | ((i >> 1) & 2)); }
+  __host__ __device__ static constexpr int y(int i) { return 8 * (((i >> 1) & 1) | ((i >> 2) & 2)); }
+};
+
+// Stage the record of Gaussian g (g >= n: a splat that blends nowhere, since
+// its t < 0 skips it) as entry q, with the cells of the TILE x TILE tile at
+// (x0, y0) that it reaches.
+template <int TILE, class Lds>
+__device__ __forceinline__ void fwd_stage(Lds& L, int q, const float* __restrict__ splats,
+                                          uint32_t g, int64_t n, float x0, float y0) {
+  float4 r0 = make_float4(0.f, 0.f, 1.f, 0.f), r1 = make_float4(1.f, -1.f, 0.f, 0.f);
+  float4 r2 = make_float4(0.f, 0.f, 0.f, 0.f);
+  float band = 0.f;
+  uint32_t cells = 0;
+  if ((int64_t)g < n) {
+    const float4* r = reinterpret_cast<const float4*>(splats + (size_t)g * GS_SPLAT_FLOATS);
+    r0 = r[0];
+    r1 = r[1];
+    r2 = r[2];
+    band = skip_band(r0.z, r0.w, r1.x, r1.y);
+    cells = cells_reached<8, 8, TILE * TILE / 64>(x0, y0, r0, r1.x, r1.y, band, FwdCells::x,
+                                                  FwdCells::y);
+  }
+  L.t[q] = r1.y;
+  L.cells[q] = cells;
+  L.s0[q] = make_float4(r0.x, r0.y, r0.z, r0.w + r0.w);  // exact
+  L.s1[q] = make_float4(r1.x, r1.y - band, r1.y + band, r1.z);
+  L.s2[q] = make_float4(r2.x, r2.y, r2.z, r1.w);
+}
 
 // The forward that writes its tile lists (from the binning's column runs):
 // the batch's Gaussian ids and the block-scan words.
@@ -248,8 +355,23 @@ constexpr int kCkptVals = 5;
 // binning) and the forward writes each batch's entries to `dvals` (vals is
 // not read): every list position up to the last one staged, which covers
 // every pixel's n_contrib.
+//
+// What bounds it: VALU issue where the lists are dense (27 operations per
+// pixel and splat; at 1M Gaussians of the surface scene a splat of a list
+// reaches 96% of its tile's cells), and the serial walk of the longest lists
+// where splats are small (a third to a half of the cells reached). So a
+// wavefront owns whole 8 x 8 cells and walks only the splats that reach them,
+// four at a time: the shapes, Q and alpha of one splat do not wait for the
+// blend of the one before, and the colours are read into the registers that
+// the shapes needed. Decisions are 64-bit lane masks in scalar registers, and
+// the position of a pixel's last blend is one bit per splat walked. Against
+// one splat per step over 16 x 4 strips, all of the list: 393 -> 299 us at
+// 1920x1080, 344 -> 254 us at 1600x1066 (1M Gaussians, lists as the binning
+// left them), 332 -> 138 us at 300k Gaussians of about their spacing's size.
+// Groups of two: 303, 260 and 151 us; four with the colours read together
+// with the shapes (96 registers): 321, 281 and 133 us.
 template <int TILE, int PX, bool CKPT = false, int NB = kFwdBatch, bool DEF = false>
-__device__ __forceinline__ void fwd_tile(FwdLdsT<NB>& L, int tile,
+__device__ __forceinline__ void fwd_tile(FwdLdsT<NB, TILE * TILE / PX>& L, int tile,
                                          const float* __restrict__ splats,
                                          const uint32_t* __restrict__ vals,
                                          const uint32_t* __restrict__ ranges, int64_t n, int W,
@@ -263,25 +385,29 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB>& L, int tile,
                                          RunLists rl = {}, uint32_t* __restrict__ dvals = nullptr) {
 #pragma clang fp contract(fast)
   constexpr int NTH = TILE * TILE / PX;
-  float4* s0 = L.s0;
-  float4* s1 = L.s1;
-  float4* s2 = L.s2;
+  constexpr int G = kFwdGroup;
+  static_assert(G == 4 && NB % G == 0, "a group's list entries are one 16-byte word");
   const int tx = tile / tiles_y, ty = tile % tiles_y;
+  const float x0 = (float)(tx * TILE), y0 = (float)(ty * TILE);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  uint32_t* const list = L.list[wv];
   const uint32_t start = ranges[tile], end = ranges[tile + 1];
   float px[PX], py[PX], T[PX], C0[PX], C1[PX], C2[PX], D[PX];
-  uint32_t last[PX];  // one past the list position of the last blended splat
-  bool done[PX];
-  bool alldone = true;
+  uint32_t last[PX];   // one past the list position of the last blended splat
+  uint64_t done[PX];   // the lanes whose pixel j takes no more splats
+  bool alldone = true;  // uniform
 #pragma unroll
   for (int j = 0; j < PX; ++j) {
-    const int pi = threadIdx.x + j * NTH;
-    const int x = tx * TILE + pi % TILE, y = ty * TILE + pi / TILE;
+    const int x = tx * TILE + FwdCells::x(wv * PX + j) + lane % 8;
+    const int y = ty * TILE + FwdCells::y(wv * PX + j) + lane / 8;
     px[j] = (float)x + 0.5f;
     py[j] = (float)y + 0.5f;
     T[j] = 1.f; C0[j] = C1[j] = C2[j] = D[j] = 0.f; last[j] = 0;
-    done[j] = !(x < W && y < H);
-    alldone &= done[j];
+    done[j] = __ballot(!(x < W && y < H));
+    alldone = alldone && done[j] == ~0ull;
   }
+  if (threadIdx.x == 0) fwd_stage<TILE>(L, NB, splats, 0u, 0, 0.f, 0.f);  // the filler
   DefCursor cur{};
   if constexpr (DEF) {
     if (start < end) def_start<NTH>(rl, cur, tx, tiles_y, ty, start);
@@ -293,79 +419,138 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB>& L, int tile,
     for (int q = threadIdx.x; q < cnt; q += NTH) {
       uint32_t g;
       if constexpr (DEF) g = DL->sid[q]; else g = vals[b + q];
-      if ((int64_t)g < n) {
-        const float4* r = reinterpret_cast<const float4*>(splats + (size_t)g * GS_SPLAT_FLOATS);
-        // staged as (u, v, a, 2 b), (c, t, o, z), (r, g, b, skip band)
-        float4 r0 = r[0];
-        const float4 r1 = r[1];
-        float4 r2 = r[2];
-        r2.w = skip_band(r0.z, r0.w, r1.x, r1.y);
-        r0.w = r0.w + r0.w;  // exact
-        s0[q] = r0;
-        s1[q] = r1;
-        s2[q] = r2;
-      } else {  // never for a correct list: an empty splat (t < 0 skips it)
-        s0[q] = make_float4(0.f, 0.f, 1.f, 0.f);
-        s1[q] = make_float4(1.f, -1.f, 0.f, 0.f);
-        s2[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+      fwd_stage<TILE>(L, q, splats, g, n, x0, y0);
     }
     __syncthreads();
-    for (int k = 0; k < cnt && !alldone; ++k) {
-      const float4 a0 = s0[k], a1 = s1[k];
-      const float4 a2 = s2[k];
-      const float b2 = a0.w;
-      if (CKPT) {
-        const uint32_t pos = b + (uint32_t)k - start;
-        if ((pos % kCkptInterval) == 0) {
-          const uint32_t bk = pos / kCkptInterval;
+    if (alldone) continue;
+    // the wavefront's list: the splats that reach its cells, in order (with
+    // CKPT every splat, since a checkpoint is due at fixed positions)
+    int m = 0;
+    for (int base = 0; base < cnt; base += kWave) {
+      constexpr uint32_t kMine = (1u << PX) - 1u;
+      const int q = base + lane;
+      const bool reach =
+          q < cnt && (CKPT || ((L.cells[min(q, NB)] >> (wv * PX)) & kMine) != 0u);
+      const uint64_t bal = __ballot(reach);
+      if (reach)
+        list[m + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                           __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))] =
+            16u * (uint32_t)q;
+      m += (int)__popcll(bal);
+    }
+    if (lane < G) list[m + lane] = 16u * NB;
+    __builtin_amdgcn_wave_barrier();  // a wavefront's LDS operations complete in order
+    const uint32_t rel = b - start;
+    for (int i0 = 0; i0 < m && !alldone; i0 += 32) {
+      const int i1 = min(i0 + 32, m);
+      uint32_t hist[PX];  // per splat walked, newest in bit 0: not blended
+#pragma unroll
+      for (int j = 0; j < PX; ++j) hist[j] = ~0u;
+      int i = i0;
+      for (; i < i1 && !alldone; i += G) {
+        uint32_t off[G];
+        float4 a0[G], a1[G], a2[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          off[g] = list[i + g];
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          a0[g] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(L.s0) + off[g]);
+          a1[g] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(L.s1) + off[g]);
+        }
+        float Q[G][PX];
+        uint64_t skip[G][PX], near = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
 #pragma unroll
           for (int j = 0; j < PX; ++j) {
-            if (done[j] || bk >= (uint32_t)nbk) continue;
-            constexpr int NP = TILE * TILE;
-            float* c = ckpt + ((size_t)tile * nbk + bk) * kCkptVals * NP + threadIdx.x + j * NTH;
-            c[0] = T[j];
-            c[NP] = C0[j];
-            c[2 * NP] = C1[j];
-            c[3 * NP] = C2[j];
-            c[4 * NP] = D[j];
+            Q[g][j] = eval_q(px[j], py[j], a0[g].x, a0[g].y, a0[g].z, a0[g].w, a1[g].x).Q;
+            skip[g][j] = __ballot(Q[g][j] > a1[g].z);
+            near |= ~(skip[g][j] | __ballot(Q[g][j] <= a1[g].y));
+          }
+        if (near != 0) {  // a few groups in a thousand: the FP64 decision
+          asm volatile("");  // not to be computed ahead of the branch
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const int q = (int)(off[g] / 16u);
+            const float4 e0 = L.s0[q], e1 = L.s1[q];
+            const float t = L.t[q];
+#pragma unroll
+            for (int j = 0; j < PX; ++j)
+              skip[g][j] =
+                  __ballot(skips_f64(t, px[j], py[j], e0.x, e0.y, e0.z, 0.5f * e0.w, e1.x));
+          }
+        }
+        // the colours are read only now, into the registers that the shapes
+        // needed until here, while alpha is formed
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+          a2[g] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(L.s2) + off[g]);
+        float al[G][PX];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int j = 0; j < PX; ++j) al[g][j] = fminf(kAlphaMax, a1[g].w * gauss(Q[g][j]));
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          if (CKPT) {
+            const uint32_t pos = rel + off[g] / 16u;
+            if (off[g] < 16u * NB && (pos % kCkptInterval) == 0) {
+              const uint32_t bk = pos / kCkptInterval;
+#pragma unroll
+              for (int j = 0; j < PX; ++j) {
+                if (__builtin_amdgcn_inverse_ballot_w64(done[j]) || bk >= (uint32_t)nbk) continue;
+                constexpr int NP = TILE * TILE;
+                const int pi = (FwdCells::y(wv * PX + j) + lane / 8) * TILE +
+                               FwdCells::x(wv * PX + j) + lane % 8;
+                float* c = ckpt + ((size_t)tile * nbk + bk) * kCkptVals * NP + pi;
+                c[0] = T[j];
+                c[NP] = C0[j];
+                c[2 * NP] = C1[j];
+                c[3 * NP] = C2[j];
+                c[4 * NP] = D[j];
+              }
+            }
+          }
+          // the step in select form: every pixel runs it, and a skipped,
+          // stopped or finished pixel changes nothing (the same decisions as
+          // fwd_step, without divergent branches)
+          alldone = true;
+#pragma unroll
+          for (int j = 0; j < PX; ++j) {
+            const float Tn = T[j] * (1.f - al[g][j]);
+            const uint64_t low = __ballot(Tn < kTStop);
+            const uint64_t none = skip[g][j] | done[j] | low;  // no blend
+            done[j] |= low & ~skip[g][j];
+            const bool nb = __builtin_amdgcn_inverse_ballot_w64(none);
+            // weight 0 when not blending: adding c * 0 leaves the sums unchanged
+            const float w = nb ? 0.f : al[g][j] * T[j];
+            C0[j] = fmaf(a2[g].x, w, C0[j]);
+            C1[j] = fmaf(a2[g].y, w, C1[j]);
+            C2[j] = fmaf(a2[g].z, w, C2[j]);
+            D[j] = fmaf(a2[g].w, w, D[j]);
+            T[j] = nb ? T[j] : Tn;
+            hist[j] = shift_in(hist[j], none);
+            // a blend in a bucket without a checkpoint: the backward would need it
+            if (CKPT && !nb && rel + off[g] / 16u >= (uint32_t)nbk * kCkptInterval)
+              atomicOr(ovf, 1u);
+            alldone = alldone && done[j] == ~0ull;
           }
         }
       }
-      // the step in select form: every pixel runs it, and a skipped, stopped
-      // or finished pixel changes nothing (the same decisions as fwd_step,
-      // without divergent branches)
-      alldone = true;
-      const uint32_t posn = b + (uint32_t)k - start + 1u;
+      // the newest clear bit of hist is the last blend: the splat that many
+      // before the last one walked
 #pragma unroll
-      for (int j = 0; j < PX; ++j) {
-        const SplatQ q = eval_q(px[j], py[j], a0.x, a0.y, a0.z, b2, a1.x);
-        const bool live = !done[j] && !splat_skips_band(q.Q, a2.w, a1.y, px[j], py[j], a0.x,
-                                                        a0.y, a0.z, 0.5f * b2, a1.x);
-        const float al = fminf(kAlphaMax, a1.z * gauss(q.Q));
-        const float Tn = T[j] * (1.f - al);
-        const bool stop = live && Tn < kTStop;
-        const bool blend = live && !stop;
-        // weight 0 when not blending: adding c * 0 leaves the sums unchanged
-        const float w = blend ? al * T[j] : 0.f;
-        C0[j] = fmaf(a2.x, w, C0[j]);
-        C1[j] = fmaf(a2.y, w, C1[j]);
-        C2[j] = fmaf(a2.z, w, C2[j]);
-        D[j] = fmaf(a1.w, w, D[j]);
-        T[j] = blend ? Tn : T[j];
-        last[j] = blend ? posn : last[j];
-        done[j] = done[j] || stop;
-        // a blend in a bucket without a checkpoint: the backward would need it
-        if (CKPT && blend && posn > (uint32_t)nbk * kCkptInterval) atomicOr(ovf, 1u);
-        alldone &= done[j];
-      }
+      for (int j = 0; j < PX; ++j)
+        if (~hist[j] != 0u) last[j] = rel + list[i - 1 - __builtin_ctz(~hist[j])] / 16u + 1u;
     }
   }
   const size_t HW = (size_t)H * W;
 #pragma unroll
   for (int j = 0; j < PX; ++j) {
-    const int pi = threadIdx.x + j * NTH;
-    const int x = tx * TILE + pi % TILE, y = ty * TILE + pi / TILE;
+    const int x = tx * TILE + FwdCells::x(wv * PX + j) + lane % 8;
+    const int y = ty * TILE + FwdCells::y(wv * PX + j) + lane / 8;
     if (x < W && y < H) {
       const size_t p = (size_t)y * W + x;
       image[p] = fmaf(T[j], bg0, C0[j]);
@@ -378,24 +563,34 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB>& L, int tile,
   }
 }
 
+// Wavefronts per SIMD the forward is compiled for. 7 (72 registers, nothing
+// spilled) against 8 (64, a few registers of the staging spilled) at 16-pixel
+// tiles: 299 against 300 us on the 1920x1080 view of the surface scene, 138
+// against 145 us at 300k Gaussians of about their spacing's size. 32-pixel
+// tiles have 16 wavefronts to a workgroup: two of them need 8 (372 against 455
+// us with one). With several pixels per lane the registers decide.
+constexpr int fwd_waves(int tile, int px) { return px > 1 ? 1 : tile == 32 ? 8 : 7; }
+
 template <int TILE, int PX>
-__global__ void __launch_bounds__(TILE* TILE / PX) k_render_fwd(
+__global__ void __launch_bounds__(TILE* TILE / PX)
+__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd(
     const float* __restrict__ splats, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ ranges, int64_t n, int W, int H, int tiles_y, float bg0,
     float bg1, float bg2, float* __restrict__ image, float* __restrict__ depth,
     float* __restrict__ T_final, uint32_t* __restrict__ n_contrib) {
-  __shared__ FwdLds L;
+  __shared__ FwdLdsT<kFwdBatch, TILE * TILE / PX> L;
   fwd_tile<TILE, PX>(L, blockIdx.x, splats, vals, ranges, n, W, H, tiles_y, bg0, bg1, bg2, image,
                      depth, T_final, n_contrib);
 }
 
 template <int TILE, int PX>
-__global__ void __launch_bounds__(TILE* TILE / PX) k_render_fwd_def(
+__global__ void __launch_bounds__(TILE* TILE / PX)
+__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_def(
     const float* __restrict__ splats, RunLists rl, uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ ranges, int64_t n, int W, int H, int tiles_y, float bg0,
     float bg1, float bg2, float* __restrict__ image, float* __restrict__ depth,
     float* __restrict__ T_final, uint32_t* __restrict__ n_contrib) {
-  __shared__ FwdLds L;
+  __shared__ FwdLdsT<kFwdBatch, TILE * TILE / PX> L;
   __shared__ DefLds<kFwdBatch, TILE * TILE / PX> DL;
   fwd_tile<TILE, PX, false, kFwdBatch, true>(L, blockIdx.x, splats, nullptr, ranges, n, W, H,
                                              tiles_y, bg0, bg1, bg2, image, depth, T_final,
@@ -408,7 +603,7 @@ __global__ void __launch_bounds__(256) k_render_fwd_ckpt(
     float bg1, float bg2, float* __restrict__ image, float* __restrict__ depth,
     float* __restrict__ T_final, uint32_t* __restrict__ n_contrib, float* __restrict__ ckpt,
     int nbk, uint32_t* __restrict__ ovf) {
-  __shared__ FwdLds L;
+  __shared__ FwdLdsT<kFwdBatch, 256> L;
   fwd_tile<16, 1, true>(L, blockIdx.x, splats, vals, ranges, n, W, H, tiles_y, bg0, bg1, bg2,
                         image, depth, T_final, n_contrib, ckpt, nbk, ovf);
 }
@@ -1014,11 +1209,12 @@ __device__ __forceinline__ int view_of(const ViewSet& vs, int it) {
 }
 
 template <int TILE, int PX, int NB>
-__global__ void __launch_bounds__(TILE* TILE / PX) k_render_fwd_batched(ViewSet vs, int64_t n,
+__global__ void __launch_bounds__(TILE* TILE / PX)
+__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched(ViewSet vs, int64_t n,
                                                                          float bg0, float bg1,
                                                                          float bg2,
                                                                          uint32_t* queue) {
-  __shared__ FwdLdsT<NB> L;
+  __shared__ FwdLdsT<NB, TILE * TILE / PX> L;
   __shared__ int s_item;
   for (int it; (it = next_item(queue, vs.total, &s_item)) >= 0;) {
     const int v = view_of(vs, it);
@@ -1031,11 +1227,12 @@ __global__ void __launch_bounds__(TILE* TILE / PX) k_render_fwd_batched(ViewSet 
 // The batched forward on the lists of the deferred binning (one run table
 // per view); each view's vals receives the list positions it stages.
 template <int TILE, int PX, int NB>
-__global__ void __launch_bounds__(TILE* TILE / PX) k_render_fwd_batched_def(ViewSet vs, int64_t n,
+__global__ void __launch_bounds__(TILE* TILE / PX)
+__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched_def(ViewSet vs, int64_t n,
                                                                              float bg0, float bg1,
                                                                              float bg2,
                                                                              uint32_t* queue) {
-  __shared__ FwdLdsT<NB> L;
+  __shared__ FwdLdsT<NB, TILE * TILE / PX> L;
   __shared__ DefLds<NB, TILE * TILE / PX> DL;
   __shared__ int s_item;
   for (int it; (it = next_item(queue, vs.total, &s_item)) >= 0;) {
