@@ -193,10 +193,10 @@ gs_status gs_render_fwd_deferred(const float* splats, int64_t n, const void* wor
 
 /* Backward (Sec. 2.2): gradients of a loss L given dL/dimage and
  * dL/ddepth, with the per-pixel transmittance recomputed from T_final
- * instead of being stored; per-splat terms are summed across each
- * wavefront (DPP) and across the tile's wavefronts (LDS) before one FP64
- * global add per (splat, tile, component); then the per-Gaussian chain rule
- * (FP64 inside) back to the 3D parameters.
+ * instead of being stored; per-splat terms are summed across a wavefront,
+ * which takes a tile or a part of one, before one FP64 global add per
+ * (splat, part, component); then the per-Gaussian chain rule (FP64 inside)
+ * back to the 3D parameters.
  *   g, n, sh_degree, cam        as given to gs_preprocess
  *   splats, vals, ranges        as produced by the forward
  *   bg (host), T_final, n_contrib  as given to / produced by gs_render_fwd
@@ -647,16 +647,18 @@ gs_status gs_tile_count_variant(const float* splats, int64_t n, const gs_camera*
 /* Kernel tuning knobs, held per host thread: gs_set_tuning sets the calling
  * thread's knobs, which that thread's later launches read (a new thread
  * starts from the defaults; the autotuner sets them). Pixels per lane of
- * the compositing kernels: fwd_px, bwd_px in {1, 2, 4} (a 16x16 or 32x32 tile runs with tile*tile/px threads; 8x8
- * tiles always use 1, 32x32 tiles at least 2 in the backward);
- * persist_wgs in 1..32: workgroups per compute unit of the persistent
- * batched launches; seq_walk 0 or 1: the tile-set walks of preprocess and
+ * the compositing kernels: fwd_px, bwd_px in {1, 2, 4} (the forward runs a
+ * 16x16 or 32x32 tile with tile*tile/px threads, the backward with a
+ * wavefront per 64 px pixels; 8x8 tiles always use 1, 32x32 tiles at least
+ * 2 in the backward); persist_wgs in 1..32: workgroups per compute unit of
+ * the persistent batched launches (backward: wavefronts, times the number a
+ * tile takes); seq_walk 0 or 1: the tile-set walks of preprocess and
  * binning run load-balanced (0: a wavefront flattens the SnugBox columns of
  * its 64 Gaussians and walks them 64 at a time, Sec. 2.1 load-balanced
  * writing) or sequentially (1: each lane walks its own Gaussian's columns,
  * the baseline that load balancing replaces). Results do not depend on the
- * knobs. fwd_batch, bwd_batch: the splats staged in LDS per batch by the
- * batched compositing launches (see the fields). Defaults: fwd_px 1, bwd_px
+ * knobs. fwd_batch: the splats staged in LDS per batch by the batched
+ * forward; bwd_batch: see the field. Defaults: fwd_px 1, bwd_px
  * 4, persist_wgs 12, seq_walk 0, fwd_batch 0, bwd_batch 0. */
 typedef struct gs_tuning {
   int32_t fwd_px;
@@ -664,8 +666,8 @@ typedef struct gs_tuning {
   int32_t persist_wgs;
   int32_t seq_walk;
   int32_t fwd_batch;  /* batched forward: splats per LDS batch, 64, 128 or 256 (0: 256) */
-  int32_t bwd_batch;  /* batched backward: splats per LDS batch, 32, 64 or 128 (0: the
-                         workgroup size's default, 32 or 64; 128 applies up to 256 threads) */
+  int32_t bwd_batch;  /* 0, 32, 64 or 128; accepted, without effect: a wavefront of the
+                         backward stages 64 list entries, one per lane */
   int32_t reserved[2];
 } gs_tuning;
 gs_status gs_set_tuning(const gs_tuning* t);

@@ -5,19 +5,21 @@
 // every wavefront walks the batch's splats that reach its pixels front to
 // back. The workgroup stops as soon as every pixel has reached T < 1e-4.
 //
-// Backward: one workgroup per tile, PX pixels per lane, walking the tile's
-// list back to front from each pixel's last contributor. The transmittance
+// Backward: one wavefront per region of a tile, PX pixels per lane, walking the
+// tile's list back to front from each pixel's last contributor. The transmittance
 // in front of each splat is recomputed as T / (1 - alpha) from the stored
 // final transmittance (nothing per splat is stored by the forward), and the
 // colour and depth behind it are accumulated on the way. The per-splat
-// gradient components are summed over each row of 16 lanes with DPP, the
-// rows' sums are parked in LDS, and after each batch one FP64 atomic add per
-// (splat, component) carries the tile's total.
+// gradient components are summed over the wavefront and parked in LDS, and
+// after each batch one FP64 atomic add per (splat, component) carries the
+// region's total.
 //
 // The FP32 arithmetic here may be contracted to FMAs; alpha is computed by
 // the same expression (explicit fmaf) in both kernels, so the backward
 // replays exactly the forward's alphas.
 #include <math.h>
+
+#include <type_traits>
 
 #include "binning.h"
 #include "common.h"
@@ -817,68 +819,177 @@ __host__ __device__ constexpr int rs_slot(int l) {
   return 4 * (l & 1) + 2 * ((l >> 1) & 1) + ((l >> 2) & 1);
 }
 
-// splats per LDS batch of the backward by default: 32 for one-wavefront
-// workgroups (more of them fit on a compute unit), 64 otherwise (fewer
-// barriers per splat)
-template <int TILE, int PX>
-constexpr int bwd_batch_default() { return TILE * TILE / PX <= 64 ? 32 : 64; }
+// Sum of x over the four rows of 16 lanes, row 0 first, in every row.
+__device__ __forceinline__ float rows_sum(float x) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const uint32_t u = __float_as_uint(x);
+  const u2 h = __builtin_amdgcn_permlane32_swap(u, u, false, false);      // rows 0 1 0 1, 2 3 2 3
+  const u2 a = __builtin_amdgcn_permlane16_swap(h.x, h.x, false, false);  // row 0, row 1
+  const u2 b = __builtin_amdgcn_permlane16_swap(h.y, h.y, false, false);  // row 2, row 3
+  return ((__uint_as_float(a.x) + __uint_as_float(a.y)) + __uint_as_float(b.x)) +
+         __uint_as_float(b.y);
+}
 
-template <int TILE, int PX, int NBV = bwd_batch_default<TILE, PX>()>
+// The backward's unit of work is a region of 16 x 4 PX pixels of a tile (8 x 8
+// for 8-pixel tiles), walked by one wavefront on its own: PX cells of 16 x 4
+// pixels, one pixel per lane (lane l at column l % 16 and row l / 16), stacked
+// so that a lane's pixels share their column. (8 x 8 cells would be reached
+// about 11% less often, but a lane's pixels would not share dx.)
+constexpr int kBwdBatch = 64;  // list entries a wavefront stages at a time, one per lane
+constexpr int kBwdGroup = 2;   // splats evaluated together with one pixel per lane
+
+// The staged splats that reach the region, in list order. Entry kBwdBatch holds
+// a splat that blends nowhere: it fills up the last group.
 struct BwdLds {
-  static constexpr int NR = TILE * TILE / PX / 16;  // rows of 16 lanes
-  static constexpr int NB = NBV;
-  float4 s0[NB], s1[NB], s2[NB];
-  uint32_t sid[NB];
-  float red[NR][GS_GRAD2D_COMPONENTS][NB];
-  uint32_t smax;
+  float4 s0[kBwdBatch + 1], s1[kBwdBatch + 1], s2[kBwdBatch + 1];  // (u, v, a, b), (c, t - band, t + band, o), (r, g, b, z)
+  float t[kBwdBatch + 1];
+  uint32_t sid[kBwdBatch + 1], pos[kBwdBatch + 1], cells[kBwdBatch + 1];
+  float red[GS_GRAD2D_COMPONENTS][kBwdBatch + 1];  // the region's sums per splat
 };
 
-// Backward of one tile (column-major id `tile`) by the whole workgroup.
-template <int TILE, int PX, bool DEPTH, int NBV = bwd_batch_default<TILE, PX>()>
-__device__ __forceinline__ void bwd_tile(BwdLds<TILE, PX, NBV>& L, int tile,
-                                         const float* __restrict__ splats,
-                                         const uint32_t* __restrict__ vals,
-                                         const uint32_t* __restrict__ ranges, int W, int H,
-                                         int tiles_y, float bg0, float bg1, float bg2,
-                                         const float* __restrict__ T_final,
-                                         const uint32_t* __restrict__ n_contrib,
-                                         const float* __restrict__ dL_dimage,
-                                         const float* __restrict__ dL_ddepth,
-                                         double* __restrict__ grad2d, int64_t n) {
-#pragma clang fp contract(fast)
-  constexpr int NTH = TILE * TILE / PX;   // threads
-  constexpr int NR = BwdLds<TILE, PX, NBV>::NR;
-  constexpr int NB = BwdLds<TILE, PX, NBV>::NB;
-  constexpr int NC = GS_GRAD2D_COMPONENTS;
-  static_assert(NTH % kWave == 0, "whole wavefronts");
-  float4* s0 = L.s0;
-  float4* s1 = L.s1;
-  float4* s2 = L.s2;
-  uint32_t* sid = L.sid;
-  auto& red = L.red;
-  uint32_t& smax = L.smax;
-  const int tx = tile / tiles_y, ty = tile % tiles_y;
-  const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-  const int row = wv * (kWave / 16) + lane / 16;
-  // lanes 0..7 of a row store the reduce-scattered sums, lanes 8 and 9 the
-  // sums of components 8 and 9
+template <int TILE>
+constexpr int bwd_cell_width() { return TILE < 16 ? TILE : 16; }
+// regions of a tile with PX cells each, and their pixel offsets in the tile
+template <int TILE, int PX>
+constexpr int bwd_regions() { return TILE * TILE / (64 * PX); }
+template <int TILE, int PX>
+__device__ __forceinline__ int bwd_region_x(int r) {
+  return TILE < 32 ? 0 : 16 * (r & 1);
+}
+template <int TILE, int PX>
+__device__ __forceinline__ int bwd_region_y(int r) {
+  return 4 * PX * (TILE < 32 ? r : r >> 1);
+}
+
+// One (splat, pixel) term of the backward, from the splat's G = exp(-Q / 2)
+// (0: the pixel does not blend it): the pixel's T and U are moved in front of
+// the splat; tg is dL/dQ / (-o / 2), w the blend weight. The order of every
+// operation is written out, here and in the sums below, so that the gradients
+// do not depend on which of the walks forms them.
+template <bool DEPTH>
+__device__ __forceinline__ void bwd_pixel(float G, float o, float4 a2, float dC0, float dC1,
+                                          float dC2, float dD, float& T, float& U, float& tg,
+                                          float& w) {
+#pragma clang fp contract(off)
+  const float oG = o * G;
+  const float al = fminf(kAlphaMax, oG);
+  const float rinv = __builtin_amdgcn_rcpf(1.f - al);
+  const float Tb = T * rinv;  // transmittance in front of this splat
+  w = al * Tb;
+  float dcc = fmaf(dC2, a2.z, fmaf(dC0, a2.x, dC1 * a2.y));
+  if (DEPTH) dcc = fmaf(dD, a2.w, dcc);
+  const float dal = rinv * fmaf(T, dcc, -U);
+  tg = oG <= kAlphaMax ? dal * G : 0.f;  // no gradient through the clamp
+  U = fmaf(w, dcc, U);
+  T = Tb;
+}
+
+// The lane's sums over its PX pixels: m0, m1, m2 of tg and its ey, ey^2 moments,
+// c of the colour and depth terms. Pixels that do not blend have tg = w = 0.
+template <int PX, bool DEPTH>
+__device__ __forceinline__ void bwd_lane_sums(const float* tg, const float* w, const float* ey,
+                                              const float* dC0, const float* dC1,
+                                              const float* dC2, const float* dD, float& m0,
+                                              float& m1, float& m2, float* c) {
+#pragma clang fp contract(off)
+  c[0] = dC0[0] * w[0];
+  c[1] = dC1[0] * w[0];
+  c[2] = dC2[0] * w[0];
+  c[3] = DEPTH ? dD[0] * w[0] : 0.f;
+  m0 = tg[0];
+  m1 = PX > 1 ? fmaf(ey[0], tg[0], ey[PX > 1 ? 1 : 0] * tg[PX > 1 ? 1 : 0]) : ey[0] * tg[0];
+  m2 = (ey[0] * tg[0]) * ey[0];
+#pragma unroll
+  for (int j = 1; j < PX; ++j) {
+    c[0] = fmaf(dC0[j], w[j], c[0]);
+    c[1] = fmaf(dC1[j], w[j], c[1]);
+    c[2] = fmaf(dC2[j], w[j], c[2]);
+    if (DEPTH) c[3] = fmaf(dD[j], w[j], c[3]);
+    m0 = m0 + tg[j];
+    if (j > 1) m1 = fmaf(ey[j], tg[j], m1);
+    m2 = fmaf(ey[j] * tg[j], ey[j], m2);
+  }
+}
+
+// The sums of a splat over the wavefront, from the lane's own sums (m0, m1, m2
+// of tg and its ey, ey^2 moments; c of the colour and depth terms), into
+// red[.][k]: within the rows of 16 lanes by DPP, then over the rows in their
+// order by lane swaps. (Measured and slower: the nine sums as products with one-hot columns
+// on the matrix cores, 16x16x4 FP32, 765 against 550 us for the image-space
+// backward of the 1M-Gaussian 1600x1066 step: nine dependent products of 32
+// cycles a splat; scattering over the rows first, eight operations fewer but
+// each waiting for the last, 560 us.)
+template <bool DEPTH, int N>
+__device__ __forceinline__ void bwd_reduce(float (&red)[GS_GRAD2D_COMPONENTS][N], int k, int lane,
+                                           float4 a0, float cc,
+                                           float o, float ex, float m0, float m1, float m2,
+                                           const float* c) {
+#pragma clang fp contract(off)
   const int l16 = lane & 15;
-  const bool rb0 = l16 & 1, rb1 = l16 & 2, rb2 = l16 & 4;
-  const int slot = l16 < 8 ? rs_slot(l16) : l16;
-  const bool writer = l16 < (DEPTH ? 10 : 9);
-  const uint32_t start = ranges[tile];
+  // dL/dQ = -o/2 tg: centroid and conic terms from the moments
+  const float nho = -0.5f * o;
+  float g[8];
+  g[0] = nho * fmaf(a0.z * ex, m0, a0.w * m1);  // times -2 in the region's sum
+  g[1] = nho * fmaf(a0.w * ex, m0, cc * m1);    // times -2 in the region's sum
+  g[2] = ((ex * ex) * nho) * m0;
+  g[3] = (ex * nho) * m1;                       // times 2 in the region's sum
+  g[4] = nho * m2;
+  g[5] = m0;
+  g[6] = c[0];
+  g[7] = c[1];
+  // lanes 0..7 of a row hold the reduce-scattered sums, lane 8 (and 9) those
+  // of components 8 (and 9)
+  const float rs = row_reduce_scatter8(g, l16 & 1, l16 & 2, l16 & 4);
+  float out = row_sum16(c[2]);
+  if (DEPTH) {
+    const float s9 = row_sum16(c[3]);
+    if (l16 == 9) out = s9;
+  }
+  out = rows_sum(l16 < 8 ? rs : out);
+  if (lane < (DEPTH ? 10 : 9)) red[lane < 8 ? rs_slot(lane) : lane][k] = out;
+}
+
+// Backward of one region of the tile whose list starts at `start` (region
+// origin x0, y0). What bounds it: VALU issue where the lists are dense (some
+// 45 operations per pixel and splat with four pixels per lane, the sums over
+// the wavefront included), the walk of the longest lists where splats are
+// small. So a wavefront stages only the splats that reach its region, reads a
+// list entry's record a batch ahead, and skips the cells that a splat does
+// not reach; splats that reach all of them take the pixels of a lane side by
+// side; with one pixel per lane two splats are evaluated together, so that
+// only T and U pass from one to the next. With the long regions of
+// bwd_region_coop, against one wavefront per tile walking the whole list:
+// 873 -> 335 us (300k Gaussians of about their spacing's size, 1600x1066),
+// 1476 -> 536 us (1M children of 100k anchors), 272 -> 90 us (1000 Gaussians,
+// 64x64), 583 -> 558 us (1M Gaussians of the surface scene, 1600x1066). With
+// 96 registers for five wavefronts a SIMD (a few spilled): 581 us for the last.
+template <int TILE, int PX, bool DEPTH>
+__device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t start,
+                                           const float* __restrict__ splats,
+                                           const uint32_t* __restrict__ vals, int W, int H,
+                                           float bg0, float bg1, float bg2,
+                                           const float* __restrict__ T_final,
+                                           const uint32_t* __restrict__ n_contrib,
+                                           const float* __restrict__ dL_dimage,
+                                           const float* __restrict__ dL_ddepth,
+                                           double* __restrict__ grad2d, int64_t n) {
+#pragma clang fp contract(fast)
+  constexpr int NB = kBwdBatch, NC = GS_GRAD2D_COMPONENTS;
+  constexpr int CW = bwd_cell_width<TILE>(), CH = 64 / CW;
+  static_assert(NB == kWave, "a batch is one entry per lane");
+  const int lane = threadIdx.x & (kWave - 1);
   const size_t HW = (size_t)H * W;
-  float px[PX], py[PX], T[PX], dC0[PX], dC1[PX], dC2[PX], dD[PX];
+  float py[PX], T[PX], dC0[PX], dC1[PX], dC2[PX], dD[PX];
   // U = dL/dC . (colour, depth) of everything behind the current splat
   // (background included): dL/dalpha (1 - alpha) = T (dL/dC . c) - U
   float U[PX];
   uint32_t nc[PX];
-  uint32_t mymax = 0;
+  uint32_t most = 0;
+  const int x = x0 + lane % CW;
+  const float px = (float)x + 0.5f;
 #pragma unroll
   for (int j = 0; j < PX; ++j) {
-    const int pi = threadIdx.x + j * NTH;
-    const int x = tx * TILE + pi % TILE, y = ty * TILE + pi / TILE;
-    px[j] = (float)x + 0.5f;
+    const int y = y0 + j * CH + lane / CW;
     py[j] = (float)y + 0.5f;
     T[j] = 1.f; dC0[j] = dC1[j] = dC2[j] = dD[j] = 0.f; nc[j] = 0;
     if (x < W && y < H) {
@@ -891,150 +1002,491 @@ __device__ __forceinline__ void bwd_tile(BwdLds<TILE, PX, NBV>& L, int tile,
       if (DEPTH) dD[j] = dL_ddepth ? dL_ddepth[p] : 0.f;
     }
     U[j] = T[j] * (dC0[j] * bg0 + dC1[j] * bg1 + dC2[j] * bg2);  // background depth is 0
-    mymax = max(mymax, nc[j]);
+    most = max(most, nc[j]);
   }
-  if (threadIdx.x == 0) smax = 0;
-  __syncthreads();
-  if (mymax) atomicMax(&smax, mymax);
-  __syncthreads();
-  const uint32_t last = start + smax;
-  for (uint32_t bend = last; bend > start;) {
-    const uint32_t bstart = bend - start > (uint32_t)NB ? bend - NB : start;
-    const int cnt = (int)(bend - bstart);
-    for (int q = threadIdx.x; q < cnt; q += NTH) {
-      const uint32_t g = vals[bstart + q];
-      if ((int64_t)g < n) {
-        // staged as (u, v, a, b), (c, t, o, skip band), (r, g, b, z)
-        const float4* r = reinterpret_cast<const float4*>(splats + (size_t)g * GS_SPLAT_FLOATS);
-        const float4 r0 = r[0];
-        float4 r1 = r[1], r2 = r[2];
-        r2.w = r1.w;
-        r1.w = skip_band(r0.z, r0.w, r1.x, r1.y);
-        s0[q] = r0;
-        s1[q] = r1;
-        s2[q] = r2;
-        sid[q] = g;
-      } else {  // never for a correct list: an empty splat with no gradient target
-        s0[q] = make_float4(0.f, 0.f, 1.f, 0.f);
-        s1[q] = make_float4(1.f, -1.f, 0.f, 0.f);
-        s2[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        sid[q] = 0xFFFFFFFFu;
-      }
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, kWave));
+  most = __builtin_amdgcn_readfirstlane(most);
+  if (lane == 0) {  // the filler: t < 0 skips it
+    L.s0[NB] = make_float4(0.f, 0.f, 1.f, 0.f);
+    L.s1[NB] = make_float4(1.f, -1.f, -1.f, 0.f);
+    L.s2[NB] = make_float4(0.f, 0.f, 0.f, 0.f);
+    L.t[NB] = -1.f;
+    L.pos[NB] = 0xFFFFFFFFu;
+  }
+  // the list from its last entry that blends down, NB entries at a time; lane
+  // l takes entry lo + l of [lo, hi). The record of the next batch and the id
+  // of the one after are read while a batch is worked on.
+  const auto entry = [&](int lo, int hi) {
+    return lo + lane < hi ? vals[start + (uint32_t)max(lo + lane, 0)] : 0xFFFFFFFFu;
+  };
+  const auto record = [&](uint32_t g, float4* r) {
+    const float4* p = reinterpret_cast<const float4*>(splats + ((int64_t)g < n ? (size_t)g : 0) *
+                                                                   GS_SPLAT_FLOATS);
+    r[0] = p[0];
+    r[1] = p[1];
+    r[2] = p[2];
+  };
+  int hi = (int)most, lo = max(hi - NB, 0);
+  uint32_t gid = entry(lo, hi);
+  float4 rec[3];
+  record(gid, rec);
+  uint32_t gid1 = entry(max(lo - NB, 0), lo);
+  while (hi > 0) {
+    // stage: the entries that reach the region, compacted in list order
+    uint32_t cells = 0;  // an id past n (never for a correct list) reaches nothing
+    float band = 0.f;
+    if ((int64_t)gid < n) {
+      band = skip_band(rec[0].z, rec[0].w, rec[1].x, rec[1].y);
+      cells = cells_reached<CW, CH, PX>((float)x0, (float)y0, rec[0], rec[1].x, rec[1].y, band,
+                                        [](int) { return 0; }, [](int i) { return CH * i; });
     }
-    __syncthreads();
-    for (int k = cnt - 1; k >= 0; --k) {
-      const uint32_t pos = bstart + (uint32_t)k - start;  // position in the tile list
-      const float4 a0 = s0[k], a1 = s1[k];
-      const float b2 = a0.w + a0.w;
-      // the PX pixels of a lane share their column: dx and a dx are common
-      const float ex = px[0] - a0.x;
-      const float aex = a0.z * ex;
-      float Qs[PX], ey[PX];
-      bool any = false;
+    const uint64_t reach = __ballot(cells != 0);
+    const int m = (int)__popcll(reach);
+    if (cells != 0) {
+      const int k = (int)__builtin_amdgcn_mbcnt_hi(
+          (uint32_t)(reach >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)reach, 0u));
+      L.s0[k] = rec[0];
+      L.s1[k] = make_float4(rec[1].x, rec[1].y - band, rec[1].y + band, rec[1].z);
+      L.s2[k] = make_float4(rec[2].x, rec[2].y, rec[2].z, rec[1].w);
+      L.t[k] = rec[1].y;
+      L.sid[k] = gid;
+      L.pos[k] = (uint32_t)(lo + lane);
+      if (PX > 1) L.cells[k] = cells;
+    }
+    __builtin_amdgcn_wave_barrier();  // a wavefront's LDS operations complete in order
+    hi = lo;
+    lo = max(lo - NB, 0);
+    gid = gid1;
+    record(gid, rec);
+    gid1 = entry(max(lo - NB, 0), lo);
+    uint64_t hit = 0;  // the staged splats that some pixel blends
+    if constexpr (PX > 1) {
+      const uint32_t mine = lane < m ? L.cells[lane] : 0u;
+      uint64_t has[PX];
 #pragma unroll
-      for (int j = 0; j < PX; ++j) {
-        ey[j] = py[j] - a0.y;
-        const float t1 = a1.x * ey[j];
-        const float td = t1 * ey[j];
-        const float Q = fmaf(ex, fmaf(b2, ey[j], aex), td);  // same value as eval_q
-        const bool act = pos < nc[j] && !splat_skips_band(Q, a1.w, a1.y, px[j], py[j], a0.x,
-                                                          a0.y, a0.z, a0.w, a1.x);
-        // an inactive pixel runs the same arithmetic with alpha = 0: no change
-        Qs[j] = act ? Q : __builtin_huge_valf();
-        any |= act;
-      }
-      float out = 0.f;
-      if (__ballot(any) != 0) {
-        float g[NC];
-        const float4 a2 = s2[k];
-        // sums over the lane's pixels of dL/dQ / (-o/2) and its ey, ey^2 moments
-        float m0, m1, m2;  // set by the first pixel
+      for (int j = 0; j < PX; ++j) has[j] = __ballot((mine >> j) & 1u);
+      const uint64_t all = __ballot(__builtin_popcount(mine) > PX / 2);
+      for (int k = m - 1; k >= 0; --k) {
+        const uint32_t pos = L.pos[k];  // position in the tile list
+        const float4 a0 = L.s0[k], a1 = L.s1[k], a2 = L.s2[k];
+        const float b2 = a0.w + a0.w;
+        const float ex = px - a0.x;
+        const float aex = a0.z * ex;
+        uint64_t act[PX], some = 0, near = 0;
+        float Q[PX], ey[PX], tg[PX], w[PX];
+        // every: all cells are reached, and the pixels of a lane go side by
+        // side; otherwise the reached cells, one after the other
+        const auto shapes = [&](auto every) {
 #pragma unroll
-        for (int j = 0; j < PX; ++j) {
-          const float G = gauss(Qs[j]);
-          const float oG = a1.z * G;
-          const float al = fminf(kAlphaMax, oG);
-          const float rinv = __builtin_amdgcn_rcpf(1.f - al);
-          const float Tb = T[j] * rinv;  // transmittance in front of this splat
-          const float w = al * Tb;
-          float dcc = dC0[j] * a2.x + dC1[j] * a2.y + dC2[j] * a2.z;
-          if (DEPTH) dcc += dD[j] * a2.w;
-          const float dal = rinv * (T[j] * dcc - U[j]);
-          const float tg = oG <= kAlphaMax ? dal * G : 0.f;  // no gradient through the clamp
-          const float tey = tg * ey[j];
-          if (j == 0) {
-            g[6] = dC0[j] * w;
-            g[7] = dC1[j] * w;
-            g[8] = dC2[j] * w;
-            if (DEPTH) g[9] = dD[j] * w;
-            m0 = tg;
-            m1 = tey;
-            m2 = tey * ey[j];
-          } else {
-            g[6] = fmaf(dC0[j], w, g[6]);
-            g[7] = fmaf(dC1[j], w, g[7]);
-            g[8] = fmaf(dC2[j], w, g[8]);
-            if (DEPTH) g[9] = fmaf(dD[j], w, g[9]);
-            m0 += tg;
-            m1 += tey;
-            m2 = fmaf(tey, ey[j], m2);
+          for (int j = 0; j < PX; ++j) {
+            act[j] = 0;
+            ey[j] = py[j] - a0.y;
+            if (!every.value && !((has[j] >> k) & 1ull)) continue;  // uniform
+            const float t1 = a1.x * ey[j];
+            const float td = t1 * ey[j];
+            Q[j] = fmaf(ex, fmaf(b2, ey[j], aex), td);  // same value as eval_q
+            const uint64_t skip = __ballot(Q[j] > a1.z);
+            near |= ~(skip | __ballot(Q[j] <= a1.y));
+            act[j] = __ballot(pos < nc[j]) & ~skip;
+            some |= act[j];
           }
-          U[j] = fmaf(w, dcc, U[j]);
-          T[j] = Tb;
+        };
+        const auto terms = [&](auto every) {
+#pragma unroll
+          for (int j = 0; j < PX; ++j) {
+            tg[j] = w[j] = 0.f;
+            if (!every.value && act[j] == 0) continue;  // uniform
+            // an inactive pixel runs the same arithmetic with alpha = 0: no change
+            const float G = gauss(
+                __builtin_amdgcn_inverse_ballot_w64(act[j]) ? Q[j] : __builtin_huge_valf());
+            bwd_pixel<DEPTH>(G, a1.w, a2, dC0[j], dC1[j], dC2[j], dD[j], T[j], U[j], tg[j],
+                             w[j]);
+          }
+        };
+        const bool every = (all >> k) & 1ull;
+        if (every) shapes(std::true_type{}); else shapes(std::false_type{});
+        if (near != 0) {  // a few splats in a thousand: the FP64 decision
+          asm volatile("");  // not to be computed ahead of the branch
+          some = 0;
+#pragma unroll
+          for (int j = 0; j < PX; ++j) {
+            const bool skip = skips_f64(L.t[k], px, py[j], a0.x, a0.y, a0.z, a0.w, a1.x);
+            act[j] = __ballot(pos < nc[j] && !skip);
+            some |= act[j];
+          }
         }
-        g[5] = m0;
-        // dL/dQ = -o/2 tg: centroid and conic terms from the moments
-        const float nho = -0.5f * a1.z;
-        g[0] = nho * (aex * m0 + a0.w * m1);          // times -2 in the tile sum
-        g[1] = nho * (a0.w * ex * m0 + a1.x * m1);    // times -2 in the tile sum
-        g[2] = nho * (ex * ex) * m0;
-        g[3] = nho * ex * m1;                         // times 2 in the tile sum
-        g[4] = nho * m2;
-        const float rs = row_reduce_scatter8(g, rb0, rb1, rb2);
-        const float s8 = row_sum16(g[8]);
-        out = l16 < 8 ? rs : s8;
-        if (DEPTH) {
-          const float s9 = row_sum16(g[9]);
-          if (l16 == 9) out = s9;
+        if (some == 0) continue;
+        hit |= 1ull << k;
+        float m0, m1, m2, c[4];
+        if (every) {
+          terms(std::true_type{});
+          bwd_lane_sums<PX, DEPTH>(tg, w, ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
+        } else {
+          terms(std::false_type{});
+          bwd_lane_sums<PX, DEPTH>(tg, w, ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
+        }
+        bwd_reduce<DEPTH>(L.red, k, lane, a0, a1.x, a1.w, ex, m0, m1, m2, c);
+      }
+    } else {
+      constexpr int G = kBwdGroup;
+      for (int k0 = m - 1; k0 >= 0; k0 -= G) {
+        int k[G];
+        float4 a0[G], a1[G], a2[G];
+        float Q[G], ex[G], ey[G];
+        uint64_t act[G], near = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          k[g] = k0 - g >= 0 ? k0 - g : NB;
+          a0[g] = L.s0[k[g]];
+          a1[g] = L.s1[k[g]];
+          a2[g] = L.s2[k[g]];
+          const uint32_t pos = L.pos[k[g]];
+          ex[g] = px - a0[g].x;
+          ey[g] = py[0] - a0[g].y;
+          const float t1 = a1[g].x * ey[g];
+          const float td = t1 * ey[g];
+          Q[g] = fmaf(ex[g], fmaf(a0[g].w + a0[g].w, ey[g], a0[g].z * ex[g]), td);
+          const uint64_t skip = __ballot(Q[g] > a1[g].z);
+          near |= ~(skip | __ballot(Q[g] <= a1[g].y));
+          act[g] = __ballot(pos < nc[0]) & ~skip;
+        }
+        if (near != 0) {
+          asm volatile("");
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const bool skip = skips_f64(L.t[k[g]], px, py[0], a0[g].x, a0[g].y, a0[g].z, a0[g].w,
+                                        a1[g].x);
+            act[g] = __ballot(L.pos[k[g]] < nc[0] && !skip);
+          }
+        }
+        float tg[G], w[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const float Gs = gauss(
+              __builtin_amdgcn_inverse_ballot_w64(act[g]) ? Q[g] : __builtin_huge_valf());
+          bwd_pixel<DEPTH>(Gs, a1[g].w, a2[g], dC0[0], dC1[0], dC2[0], dD[0], T[0], U[0], tg[g],
+                           w[g]);
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          if (act[g] == 0) continue;  // uniform
+          hit |= 1ull << k[g];
+          float m0, m1, m2, c[4];
+          bwd_lane_sums<1, DEPTH>(&tg[g], &w[g], &ey[g], dC0, dC1, dC2, dD, m0, m1, m2, c);
+          bwd_reduce<DEPTH>(L.red, k[g], lane, a0[g], a1[g].x, a1[g].w, ex[g], m0, m1, m2, c);
         }
       }
-      if (writer) red[row][slot][k] = out;
     }
-    __syncthreads();
-    // one atomic per (splat, component) for this tile, one lane per pair, so
+    __builtin_amdgcn_wave_barrier();
+    // one atomic per (splat, component) for this region, one lane per pair, so
     // that the lanes of an instruction cover the consecutive components of a
-    // few splats (a few cache lines of the per-splat records); splats no
-    // pixel of the tile blends contribute nothing and are skipped. Without
-    // depth, component 9 has no gradient (and no LDS row).
+    // few splats (a few cache lines of the per-splat records). Without depth,
+    // component 9 has no gradient.
     constexpr int NCU = DEPTH ? NC : NC - 1;
-    for (int e = threadIdx.x; e < cnt * NCU; e += NTH) {
+    for (int e = lane; e < m * NCU; e += kWave) {
       const int q = e / NCU, c = e - q * NCU;
-      const uint32_t gidx = sid[q];
-      if ((int64_t)gidx >= n) continue;
-      float a = 0.f;
-#pragma unroll
-      for (int r2 = 0; r2 < NR; ++r2) a += red[r2][c][q];
+      if (!((hit >> q) & 1ull)) continue;
+      float a = L.red[c][q];
       if (c < 2) a *= -2.f;  // exact: powers of two
       if (c == 3) a *= 2.f;
-      if (a != 0.f) unsafeAtomicAdd(grad2d + (size_t)gidx * NC + c, (double)a);
+      if (a != 0.f) unsafeAtomicAdd(grad2d + (size_t)L.sid[q] * NC + c, (double)a);
     }
-    __syncthreads();
-    bend = bstart;
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
-// Workgroup b takes tile order[b] (order null: tile b).
+// A region of four cells whose walk is long goes to a workgroup of four
+// wavefronts, one per cell: each walks the splats that reach its 16 x 4 pixels,
+// kCoopBatch list entries at a time, and leaves every lane's tg and w of each
+// in LDS; then the wavefronts share out the entries and form their sums from
+// the four cells' values, in the order in which one wavefront with four
+// pixels per lane forms them, so the gradients are the same to the bit. The
+// serial part of a walk is then a quarter of the pixels' terms instead of all
+// terms and sums. 1.6 times the work of one wavefront where every splat
+// reaches every cell, hence only for long walks.
+constexpr int kCoopBatch = 16;
+struct BwdCoopLds {
+  float4 s0[kWave + 1], s1[kWave + 1], s2[kWave + 1];  // as in BwdLds, by list entry
+  float t[kWave + 1];
+  uint32_t sid[kWave + 1], cells[kWave + 1];
+  float2 tw[kCoopBatch][4][kWave];  // (tg, w) by entry, cell and lane
+  uint32_t hit[2][4];               // per cell: the batch's entries that some pixel blends
+  float red[GS_GRAD2D_COMPONENTS][kCoopBatch];
+  uint32_t most[4];
+};
+
+template <bool DEPTH>
+__device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, uint32_t start,
+                                                const float* __restrict__ splats,
+                                                const uint32_t* __restrict__ vals, int W, int H,
+                                                float bg0, float bg1, float bg2,
+                                                const float* __restrict__ T_final,
+                                                const uint32_t* __restrict__ n_contrib,
+                                                const float* __restrict__ dL_dimage,
+                                                const float* __restrict__ dL_ddepth,
+                                                double* __restrict__ grad2d, int64_t n) {
+#pragma clang fp contract(fast)
+  constexpr int NC = GS_GRAD2D_COMPONENTS, NCU = DEPTH ? NC : NC - 1;
+  constexpr int B = kCoopBatch, G = kBwdGroup;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const size_t HW = (size_t)H * W;
+  const int x = x0 + lane % 16;
+  const float px = (float)x + 0.5f;
+  // the upstream gradients of the four cells (for the sums), and the state of
+  // this wavefront's own
+  float py[4], dC0[4], dC1[4], dC2[4], dD[4];
+  float T = 1.f, U = 0.f;
+  uint32_t nc = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int y = y0 + j * 4 + lane / 16;
+    py[j] = (float)y + 0.5f;
+    dC0[j] = dC1[j] = dC2[j] = dD[j] = 0.f;
+    if (x < W && y < H) {
+      const size_t p = (size_t)y * W + x;
+      dC0[j] = dL_dimage[p];
+      dC1[j] = dL_dimage[HW + p];
+      dC2[j] = dL_dimage[2 * HW + p];
+      if (DEPTH) dD[j] = dL_ddepth ? dL_ddepth[p] : 0.f;
+      if (j == wv) {
+        T = T_final[p];
+        nc = n_contrib[p];
+      }
+    }
+  }
+  float my_py = py[0], e0 = dC0[0], e1 = dC1[0], e2 = dC2[0], e3 = dD[0];
+#pragma unroll
+  for (int j = 1; j < 4; ++j)
+    if (wv == j) {  // uniform
+      my_py = py[j];
+      e0 = dC0[j];
+      e1 = dC1[j];
+      e2 = dC2[j];
+      e3 = dD[j];
+    }
+  U = T * (e0 * bg0 + e1 * bg1 + e2 * bg2);
+  uint32_t most = nc;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, kWave));
+  if (lane == 0) L.most[wv] = most;
+  if (threadIdx.x == 0) {  // the filler: t < 0 skips it
+    L.s0[kWave] = make_float4(0.f, 0.f, 1.f, 0.f);
+    L.s1[kWave] = make_float4(1.f, -1.f, -1.f, 0.f);
+    L.s2[kWave] = make_float4(0.f, 0.f, 0.f, 0.f);
+    L.t[kWave] = -1.f;
+  }
+  __syncthreads();
+  most = max(max(L.most[0], L.most[1]), max(L.most[2], L.most[3]));
+  most = __builtin_amdgcn_readfirstlane(most);
+  // 64 entries of the list at a time, staged by the wavefronts in turn (the
+  // next 64 are read by another wavefront while these are worked on)
+  uint32_t gid = 0xFFFFFFFFu;
+  float4 rec[3];
+  const auto fetch = [&](int lo, int hi) {
+    gid = lo + lane < hi ? vals[start + (uint32_t)(lo + lane)] : 0xFFFFFFFFu;
+    const float4* p = reinterpret_cast<const float4*>(
+        splats + ((int64_t)gid < n ? (size_t)gid : 0) * GS_SPLAT_FLOATS);
+    rec[0] = p[0];
+    rec[1] = p[1];
+    rec[2] = p[2];
+  };
+  int hi = (int)most, lo = max(hi - kWave, 0);
+  if (wv == 0 && hi > 0) fetch(lo, hi);
+  for (int turn = 0; hi > 0; ++turn) {
+    if (wv == (turn & 3)) {
+      uint32_t cells = 0;  // an id past n (never for a correct list) reaches nothing
+      if ((int64_t)gid < n) {
+        const float band = skip_band(rec[0].z, rec[0].w, rec[1].x, rec[1].y);
+        cells = cells_reached<16, 4, 4>((float)x0, (float)y0, rec[0], rec[1].x, rec[1].y, band,
+                                        [](int) { return 0; }, [](int i) { return 4 * i; });
+        L.s0[lane] = rec[0];
+        L.s1[lane] = make_float4(rec[1].x, rec[1].y - band, rec[1].y + band, rec[1].z);
+        L.s2[lane] = make_float4(rec[2].x, rec[2].y, rec[2].z, rec[1].w);
+        L.t[lane] = rec[1].y;
+        L.sid[lane] = gid;
+      }
+      L.cells[lane] = cells;
+    }
+    const int nlo = max(lo - kWave, 0);
+    if (wv == ((turn + 1) & 3) && lo > 0) fetch(nlo, lo);
+    __syncthreads();
+    const uint64_t mine = __ballot((L.cells[lane] >> wv) & 1u);
+    for (int b0 = (hi - lo - 1) / B * B, par = 0; b0 >= 0; b0 -= B, par ^= 1) {
+      // the cell's entries of this batch, last first, G at a time
+      uint32_t todo = (uint32_t)(mine >> b0) & ((1u << B) - 1u), hit = 0;
+      while (todo != 0) {
+        int k[G];
+        float4 a0[G], a1[G], a2[G];
+        float Q[G];
+        uint64_t act[G], near = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const int kb = 31 - __builtin_clz(todo | 1u);
+          k[g] = todo != 0 ? b0 + kb : kWave;
+          todo &= ~(1u << kb);
+          a0[g] = L.s0[k[g]];
+          a1[g] = L.s1[k[g]];
+          a2[g] = L.s2[k[g]];
+          const float ex = px - a0[g].x, ey = my_py - a0[g].y;
+          const float t1 = a1[g].x * ey;
+          const float td = t1 * ey;
+          Q[g] = fmaf(ex, fmaf(a0[g].w + a0[g].w, ey, a0[g].z * ex), td);  // as eval_q
+          const uint64_t skip = __ballot(Q[g] > a1[g].z);
+          near |= ~(skip | __ballot(Q[g] <= a1[g].y));
+          act[g] = __ballot((uint32_t)(lo + k[g]) < nc) & ~skip;
+        }
+        if (near != 0) {  // a few groups in a thousand: the FP64 decision
+          asm volatile("");  // not to be computed ahead of the branch
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            act[g] = __ballot((uint32_t)(lo + k[g]) < nc &&
+                              !skips_f64(L.t[k[g]], px, my_py, a0[g].x, a0[g].y, a0[g].z,
+                                         a0[g].w, a1[g].x));
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          if (act[g] == 0) continue;  // uniform (the filler's t < 0 leaves it inactive)
+          const float Gs = gauss(
+              __builtin_amdgcn_inverse_ballot_w64(act[g]) ? Q[g] : __builtin_huge_valf());
+          float2 tw;
+          bwd_pixel<DEPTH>(Gs, a1[g].w, a2[g], e0, e1, e2, e3, T, U, tw.x, tw.y);
+          L.tw[k[g] - b0][wv][lane] = tw;
+          hit |= 1u << (k[g] - b0);
+        }
+      }
+      if (lane == 0) L.hit[par][wv] = hit;
+      __syncthreads();
+      // the sums: entry q by wavefront q % 4
+      const uint32_t h0 = L.hit[par][0], h1 = L.hit[par][1], h2 = L.hit[par][2],
+                     h3 = L.hit[par][3];
+      const uint32_t any = h0 | h1 | h2 | h3;
+      for (int q = wv; q < B; q += 4) {
+        if (!(__builtin_amdgcn_readfirstlane(any >> q) & 1u)) continue;  // uniform
+        const uint32_t of = __builtin_amdgcn_readfirstlane(
+            ((h0 >> q) & 1u) | ((h1 >> q) & 1u) << 1 | ((h2 >> q) & 1u) << 2 |
+            ((h3 >> q) & 1u) << 3);
+        const float4 a0 = L.s0[b0 + q], a1 = L.s1[b0 + q];
+        float tg[4], w[4], ey[4], m0, m1, m2, c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          // a cell without a blend adds zeros
+          const float2 tw = (of >> j) & 1u ? L.tw[q][j][lane] : make_float2(0.f, 0.f);
+          tg[j] = tw.x;
+          w[j] = tw.y;
+          ey[j] = py[j] - a0.y;
+        }
+        bwd_lane_sums<4, DEPTH>(tg, w, ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
+        const float ex = px - a0.x;
+        bwd_reduce<DEPTH>(L.red, q, lane, a0, a1.x, a1.w, ex, m0, m1, m2, c);
+      }
+      __syncthreads();
+      for (int e = threadIdx.x; e < B * NCU; e += 4 * kWave) {
+        const int q = e / NCU, c = e - q * NCU;
+        if (!((any >> q) & 1u)) continue;
+        float a = L.red[c][q];
+        if (c < 2) a *= -2.f;  // exact: powers of two
+        if (c == 3) a *= 2.f;
+        if (a != 0.f) unsafeAtomicAdd(grad2d + (size_t)L.sid[b0 + q] * NC + c, (double)a);
+      }
+    }
+    __syncthreads();  // the entries are read until here
+    hi = lo;
+    lo = nlo;
+  }
+}
+
+// A launch ends when its longest walk does, and all its walks together fill
+// the chip for about (their sum) x 0.5 cycles, at some 1000 cycles per splat
+// of a walk by a single wavefront: a walk above 1 / 3072 of the sum is long
+// (the sum is taken from four quantiles of the sorted tiles' work). Measured
+// at 1 / 2048, 1 / 3072, 1 / 4096 and with no region long: 340, 335, 340 and
+// 749 us at 300k Gaussians of about their spacing's size, 540, 536, 509 and
+// 1151 us at 1M children of 100k anchors, 573, 558, 595 and 615 us at 1M
+// Gaussians of the surface scene (1600x1066 each).
+__device__ __forceinline__ uint32_t bwd_long_walk(const uint32_t* order, const uint32_t* work,
+                                                  int nt, int regions) {
+  uint32_t s = 0;
+#pragma unroll
+  for (int i = 1; i < 8; i += 2) s += work[order[(int)((int64_t)nt * i / 8)]];
+  return (uint32_t)((uint64_t)s * (uint32_t)regions / 12288u);
+}
+constexpr int kBwdSplit = 2048;  // regions, heaviest first, that may get a workgroup
+
+// The backward's launch: with four cells per region and the tiles' order known,
+// workgroups 0 .. split - 1 each look at one of the first regions and take it if
+// its tile's walk is long; the workgroups after them take the other regions,
+// one per wavefront.
+template <bool SPLIT>
+union BwdShared {
+  BwdLds one[4];
+  BwdCoopLds coop;
+};
+template <>
+union BwdShared<false> {
+  BwdLds one[4];
+};
+template <int TILE, int PX>
+constexpr bool bwd_can_split() { return PX == 4 && TILE >= 16; }
+template <int TILE, int PX>
+__host__ __device__ inline int bwd_split(int nt, bool ordered) {
+  const int r = nt * bwd_regions<TILE, PX>();
+  return !bwd_can_split<TILE, PX>() || !ordered ? 0 : r < kBwdSplit ? r : kBwdSplit;
+}
+
+// Region r of rank order: of tile order[r / R]; its part r % R.
+template <int TILE, int PX, bool DEPTH, class Shared>
+__device__ __forceinline__ void bwd_one(Shared& L, int tile, int part,
+                                        const float* __restrict__ splats,
+                                        const uint32_t* __restrict__ vals,
+                                        const uint32_t* __restrict__ ranges, int W, int H,
+                                        int tiles_y, float bg0, float bg1, float bg2,
+                                        const float* __restrict__ T_final,
+                                        const uint32_t* __restrict__ n_contrib,
+                                        const float* __restrict__ dL_dimage,
+                                        const float* __restrict__ dL_ddepth,
+                                        double* __restrict__ grad2d, int64_t n) {
+  const int x0 = tile / tiles_y * TILE + bwd_region_x<TILE, PX>(part);
+  const int y0 = tile % tiles_y * TILE + bwd_region_y<TILE, PX>(part);
+  if constexpr (std::is_same<Shared, BwdCoopLds>::value)
+    bwd_region_coop<DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1, bg2, T_final,
+                           n_contrib, dL_dimage, dL_ddepth, grad2d, n);
+  else
+    bwd_region<TILE, PX, DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1, bg2,
+                                T_final, n_contrib, dL_dimage, dL_ddepth, grad2d, n);
+}
+
+// order, work: the tiles heaviest first and each tile's largest n_contrib
+// (null: tile-id order, one wavefront per region).
 template <int TILE, int PX, bool DEPTH>
-__global__ void __launch_bounds__(TILE* TILE / PX) k_render_bwd(
+__global__ void __launch_bounds__(4 * kWave) k_render_bwd(
     const float* __restrict__ splats, const uint32_t* __restrict__ vals,
-    const uint32_t* __restrict__ ranges, int W, int H, int tiles_y, float bg0, float bg1,
+    const uint32_t* __restrict__ ranges, int W, int H, int nt, int tiles_y, float bg0, float bg1,
     float bg2, const float* __restrict__ T_final, const uint32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimage, const float* __restrict__ dL_ddepth,
-    double* __restrict__ grad2d, int64_t n, const uint32_t* __restrict__ order) {
-  __shared__ BwdLds<TILE, PX> L;
-  const int tile = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
-  bwd_tile<TILE, PX, DEPTH>(L, tile, splats, vals, ranges, W, H, tiles_y, bg0, bg1, bg2,
-                            T_final, n_contrib, dL_dimage, dL_ddepth, grad2d, n);
+    double* __restrict__ grad2d, int64_t n, const uint32_t* __restrict__ order,
+    const uint32_t* __restrict__ work) {
+  __shared__ BwdShared<bwd_can_split<TILE, PX>()> L;
+  constexpr int R = bwd_regions<TILE, PX>();
+  const int split = bwd_split<TILE, PX>(nt, order != nullptr);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const bool first = (int)blockIdx.x < split;
+  const int item = first ? (int)blockIdx.x : ((int)blockIdx.x - split) * 4 + wv;
+  if (item >= nt * R) return;
+  const int rank = item / R;
+  const int tile = order ? (int)order[rank] : rank;
+  const bool is_long = item < split && work[tile] > bwd_long_walk(order, work, nt, nt * R);
+  if (first != is_long) return;
+  if constexpr (bwd_can_split<TILE, PX>()) {
+    if (first) {
+      bwd_one<TILE, PX, DEPTH>(L.coop, tile, item % R, splats, vals, ranges, W, H, tiles_y, bg0,
+                               bg1, bg2, T_final, n_contrib, dL_dimage, dL_ddepth, grad2d, n);
+      return;
+    }
+  }
+  bwd_one<TILE, PX, DEPTH>(L.one[wv], tile, item % R, splats, vals, ranges, W, H, tiles_y, bg0,
+                           bg1, bg2, T_final, n_contrib, dL_dimage, dL_ddepth, grad2d, n);
 }
 
 // Longest-first tile order for the backward. The backward of a tile walks
@@ -1245,21 +1697,49 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched_d
   }
 }
 
-template <int TILE, int PX, bool DEPTH, int NB>
-__global__ void __launch_bounds__(TILE* TILE / PX) k_render_bwd_batched(ViewSet vs, int64_t n,
-                                                                         float bg0, float bg1,
-                                                                         float bg2,
-                                                                         uint32_t* queue,
-                                                                         const uint32_t* order) {
-  __shared__ BwdLds<TILE, PX, NB> L;
+// The backward's regions from one queue: first those that may be long, by the
+// workgroup together, then the rest, each wavefront on its own.
+template <int TILE, int PX, bool DEPTH>
+__global__ void __launch_bounds__(4 * kWave) k_render_bwd_batched(
+    ViewSet vs, int64_t n, float bg0, float bg1, float bg2, uint32_t* queue,
+    const uint32_t* __restrict__ order, const uint32_t* __restrict__ work) {
+  __shared__ BwdShared<bwd_can_split<TILE, PX>()> L;
   __shared__ int s_item;
-  for (int q; (q = next_item(queue, vs.total, &s_item)) >= 0;) {
-    const int it = order ? (int)order[q] : q;
+  constexpr int R = bwd_regions<TILE, PX>();
+  const int total = vs.total * R, split = bwd_split<TILE, PX>(vs.total, order != nullptr);
+  const uint32_t long_walk = split > 0 ? bwd_long_walk(order, work, vs.total, total) : 0u;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int q = -1;
+  if constexpr (bwd_can_split<TILE, PX>()) {
+    while ((q = next_item(queue, split + total, &s_item)) >= 0 && q < split) {
+      const int it = (int)order[q / R];
+      if (work[it] <= long_walk) continue;
+      const int v = view_of(vs, it);
+      bwd_one<TILE, PX, DEPTH>(L.coop, it - vs.start[v], q % R, vs.splats[v], vs.vals[v],
+                               vs.ranges[v], vs.W[v], vs.H[v], vs.tiles_y[v], bg0, bg1, bg2,
+                               vs.T_final[v], vs.n_contrib[v], vs.dL_dimage[v], vs.dL_ddepth[v],
+                               vs.grad2d[v], n);
+    }
+    if (q < 0) return;  // the queue is empty
+    __syncthreads();    // the regions' LDS changes hands
+  }
+  // the item taken last is the first wavefront's
+  for (bool have = bwd_can_split<TILE, PX>() && wv == 0;; have = false) {
+    if (!have) {
+      uint32_t k = 0;
+      if ((threadIdx.x & (kWave - 1)) == 0) k = atomicAdd(queue, 1u);
+      q = (int)__builtin_amdgcn_readfirstlane(k);
+    }
+    const int item = q - split;
+    if (item < 0) continue;  // never: the queue is past the split regions here
+    if (item >= total) return;
+    const int it = order ? (int)order[item / R] : item / R;
+    if (item < split && work[it] > long_walk) continue;  // done by a workgroup
     const int v = view_of(vs, it);
-    bwd_tile<TILE, PX, DEPTH, NB>(L, it - vs.start[v], vs.splats[v], vs.vals[v], vs.ranges[v],
-                              vs.W[v], vs.H[v], vs.tiles_y[v], bg0, bg1, bg2, vs.T_final[v],
-                              vs.n_contrib[v], vs.dL_dimage[v], vs.dL_ddepth[v], vs.grad2d[v],
-                              n);
+    bwd_one<TILE, PX, DEPTH>(L.one[wv], it - vs.start[v], item % R, vs.splats[v], vs.vals[v],
+                             vs.ranges[v], vs.W[v], vs.H[v], vs.tiles_y[v], bg0, bg1, bg2,
+                             vs.T_final[v], vs.n_contrib[v], vs.dL_dimage[v], vs.dL_ddepth[v],
+                             vs.grad2d[v], n);
   }
 }
 
@@ -1393,12 +1873,13 @@ static gs_status image_bwd(int64_t n, const CamDev& cd, const float* splats, con
     order = tile_order;
   }
 #define GS_BWD2(TL, PXV, DEP)                                                                  \
-  k_render_bwd<TL, PXV, DEP><<<nt, TL * TL / PXV, 0, st>>>(                                 \
-      splats, vals, ranges, cd.W, cd.H, cd.tiles_y, bg[0], bg[1], bg[2], T_final, n_contrib, \
-      dL_dimage, dL_ddepth, grad2d, n, order)
+  k_render_bwd<TL, PXV, DEP><<<bwd_split<TL, PXV>(nt, order != nullptr) +                      \
+                                   div_up((int64_t)nt * bwd_regions<TL, PXV>(), 4),            \
+                               4 * kWave, 0, st>>>(                                            \
+      splats, vals, ranges, cd.W, cd.H, nt, cd.tiles_y, bg[0], bg[1], bg[2], T_final,          \
+      n_contrib, dL_dimage, dL_ddepth, grad2d, n, order, order ? tile_order + nt : nullptr)
 #define GS_BWD(TL, PXV) \
   if (dL_ddepth) GS_BWD2(TL, PXV, true); else GS_BWD2(TL, PXV, false)
-  // 32x32 tiles with one pixel per lane would need 160 KB of LDS: use 2
   GS_TIMED("render_bwd", st, if (cd.tile == 8) { GS_BWD(8, 1); }
            else if (cd.tile == 16) {
              if (px == 4) { GS_BWD(16, 4); } else if (px == 2) { GS_BWD(16, 2); }
@@ -1690,7 +2171,6 @@ extern "C" gs_status gs_render_bwd_batched(const gs_gaussians* g, int64_t n, int
     GS_CHECK_LAUNCH();
   }
   const int px = tuning().bwd_px;
-  const int grid = persistent_grid(vs.total, tuning().persist_wgs);
   k_reset_queue<<<1, 1, 0, st>>>(queue);
   GS_CHECK_LAUNCH();
   const uint32_t* order = nullptr;
@@ -1705,19 +2185,13 @@ extern "C" gs_status gs_render_bwd_batched(const gs_gaussians* g, int64_t n, int
     GS_CHECK_LAUNCH();
     order = tile_order;
   }
-  // splat batch: the knob (32, 64, 128; 128 needs 80 KB of LDS at 256 threads
-  // and is not built for 512), else the default of the workgroup size
-  const int bb = tuning().bwd_batch;
-#define GS_BWDB3(TL, PXV, DEP, NBV)                                                          \
-  k_render_bwd_batched<TL, PXV, DEP, NBV><<<grid, TL * TL / PXV, 0, st>>>(vs, n, bg[0], bg[1], \
-                                                                          bg[2], queue, order)
-#define GS_BWDB2(TL, PXV, DEP)                                                        \
-  do {                                                                                \
-    if (bb == 32) GS_BWDB3(TL, PXV, DEP, 32);                                         \
-    else if (bb == 64) GS_BWDB3(TL, PXV, DEP, 64);                                    \
-    else if (bb == 128 && TL * TL / PXV <= 256) GS_BWDB3(TL, PXV, DEP, (TL * TL / PXV <= 256 ? 128 : 64)); \
-    else GS_BWDB3(TL, PXV, DEP, (bwd_batch_default<TL, PXV>()));                      \
-  } while (0)
+#define GS_BWDB2(TL, PXV, DEP)                                                          \
+  k_render_bwd_batched<TL, PXV, DEP><<<                                                 \
+      persistent_grid(bwd_split<TL, PXV>(vs.total, order != nullptr) +                  \
+                          vs.total * bwd_regions<TL, PXV>(),                            \
+                      div_up(tuning().persist_wgs * bwd_regions<TL, PXV>(), 4)),        \
+      4 * kWave, 0, st>>>(vs, n, bg[0], bg[1], bg[2], queue, order,                         \
+                      order ? tile_order + vs.total : nullptr)
 #define GS_BWDB(TL, PXV) \
   if (any_depth) GS_BWDB2(TL, PXV, true); else GS_BWDB2(TL, PXV, false)
   GS_TIMED("render_bwd", st, if (tile == 8) { GS_BWDB(8, 1); }
@@ -1729,7 +2203,6 @@ extern "C" gs_status gs_render_bwd_batched(const gs_gaussians* g, int64_t n, int
            });
 #undef GS_BWDB
 #undef GS_BWDB2
-#undef GS_BWDB3
   GS_CHECK_LAUNCH();
   CamDev cds[GS_MAX_VIEWS];
   const double* g2[GS_MAX_VIEWS];
