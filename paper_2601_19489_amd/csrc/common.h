@@ -339,13 +339,4 @@ __device__ __forceinline__ float skip_band(float a, float b, float c, float t) {
   return (1e-6f * (num / (float)det)) * t;
 }
 
-__device__ __forceinline__ bool splat_skips_band(float q32, float band, float t, float px,
-                                                 float py, float u, float v, float a, float b,
-                                                 float c) {
-#pragma clang fp contract(off)
-  const float diff = q32 - t;
-  if (fabsf(diff) > band) return diff > 0.f;  // decided outside the splat's band
-  return splat_skips_exact(t, px, py, u, v, a, b, c);
-}
-
 }  // namespace gs

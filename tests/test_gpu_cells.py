@@ -13,6 +13,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import densify as oden
 from oracle import render as orender
 from paper_2601_19489_amd import _lib, scenes
 
@@ -111,3 +112,32 @@ def test_lists_around_every_batch_size(tile, across, fwd_px, bwd_px):
     skip = exclusions(vals, ranges, cam, out, clamp, n)
     for k, nm in enumerate(orender.GRAD2D):
         assert_grads_close(grad2d.cpu().numpy().T[k], want[k], skip, 'grad2d.' + nm)
+
+
+@pytest.mark.parametrize('tile,across', [(8, 24), (16, 24), (32, 12)])
+def test_split_score_around_every_batch_size(tile, across):
+    """Counts under a mask that leaves out whole cells, single pixels and
+    (one column of tiles) everything: equal to the oracle's wherever no pixel's
+    decision is uncertain, within that many pixels elsewhere."""
+    W, H = across * tile - 3, across * tile - 5
+    cam = scenes.look_at_camera((0, 0, -4), (0, 0, 0), W, H, tile=tile)
+    rec, vals, ranges = _lists(across, across, tile, seed=3 + tile)
+    n = len(rec)
+    rng = np.random.default_rng(tile)
+    mask = rng.random((H, W)) < 0.4
+    cells = rng.random((-(-H // 8), -(-W // 8))) < 0.5
+    mask &= np.kron(cells, np.ones((8, 8), bool))[:H, :W]
+    mask[:, tile:2 * tile] = False
+    dev = lambda x: torch.as_tensor(x, device='cuda').contiguous()
+    score = torch.zeros(n, dtype=torch.int32, device='cuda')
+    _lib.gs_split_score(dev(rec), n, dev(vals.view(np.int32)), dev(ranges.view(np.int32)),
+                        _lib.camera(cam, tile), dev(mask.astype(np.uint8)), score)
+    torch.cuda.synchronize()
+    sp = gpu_splat_fields(rec.astype(np.float64))
+    sp['depth'] = sp['dval']
+    want, unc = oden.split_score(sp, cam, vals, ranges, mask)
+    got = score.cpu().numpy().astype(np.int64)
+    sure = unc == 0
+    assert sure.mean() > 0.95 and want.sum() > 1000
+    np.testing.assert_array_equal(got[sure], want[sure])
+    assert np.all(np.abs(got[~sure] - want[~sure]) <= unc[~sure])
