@@ -47,8 +47,10 @@ __global__ void k_mm_init(unsigned long long* mm) {
 }
 
 // min and max of non-negative doubles through their bit patterns (which
-// order like the values)
-__global__ void __launch_bounds__(256) k_mm(const double* __restrict__ v, int64_t n,
+// order like the values). One pair of atomics per workgroup of 1024, since
+// atomics on one address follow one another at some 11 ns (one pair per
+// wavefront of 1024 workgroups of 256: 95 us at any size).
+__global__ void __launch_bounds__(1024) k_mm(const double* __restrict__ v, int64_t n,
                                             unsigned long long* __restrict__ mm) {
   unsigned long long lo = ~0ull, hi = 0ull;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -62,7 +64,18 @@ __global__ void __launch_bounds__(256) k_mm(const double* __restrict__ v, int64_
     lo = ol < lo ? ol : lo;
     hi = oh > hi ? oh : hi;
   }
+  __shared__ unsigned long long part[2][1024 / kWave];
+  const int w = threadIdx.x / kWave;
   if ((threadIdx.x & (kWave - 1)) == 0) {
+    part[0][w] = lo;
+    part[1][w] = hi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < 1024 / kWave; ++k) {
+      lo = part[0][k] < lo ? part[0][k] : lo;
+      hi = part[1][k] > hi ? part[1][k] : hi;
+    }
     atomicMin(mm, lo);
     atomicMax(mm + 1, hi);
   }
@@ -72,6 +85,28 @@ struct DensArrays {
   const float *means, *ls, *quats, *op, *sh;
   float *o_means, *o_ls, *o_quats, *o_op, *o_sh;
 };
+
+// Rows of Gaussian i copied to output entries o .. o + c - 1 (the second, or
+// both if `all` is set, as zeros when `zero` is set). Eight rows are read
+// before the first is written: a store may alias the next load as far as the
+// compiler knows, and waiting for each row in turn took 333 us for 1M
+// Gaussians of 59 values (500 MB).
+__device__ __forceinline__ void copy_rows(const float* __restrict__ in, float* __restrict__ out,
+                                          int rows, int64_t n, int64_t i, int64_t n_out,
+                                          int64_t o, int c, bool zero, bool all) {
+  for (int r0 = 0; r0 < rows; r0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = r0 + j < rows ? in[(r0 + j) * n + i] : 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (r0 + j >= rows) break;  // uniform
+      float* q = out + (r0 + j) * n_out + o;
+      if (c > 0) q[0] = zero && all ? 0.f : v[j];
+      if (c > 1) q[1] = zero ? 0.f : v[j];
+    }
+  }
+}
 
 __global__ void __launch_bounds__(256) k_dens_apply(DensArrays a, int64_t n, int sh_rows,
                                                     const float* __restrict__ eps,
@@ -85,19 +120,19 @@ __global__ void __launch_bounds__(256) k_dens_apply(DensArrays a, int64_t n, int
     const int64_t base = off[i];
     const int c = kd == 3 ? 0 : (kd ? 2 : 1);
     if (base + c > n_out) continue;  // only for an inconsistent n_out
-    double s[3], mu[3];
+    float s[3], mu[3];
     for (int d = 0; d < 3; ++d) {
       s[d] = a.ls[d * n + i];
       mu[d] = a.means[d * n + i];
     }
     const bool split = kd == 2;
+    // moments of new entries (a clone's copy, both split children) start at zero
+    copy_rows(a.sh, a.o_sh, sh_rows, n, i, n_out, base, c, moments, split);
+    copy_rows(a.quats, a.o_quats, 4, n, i, n_out, base, c, moments, split);
+    copy_rows(a.op, a.o_op, 1, n, i, n_out, base, c, moments, split);
     for (int k = 0; k < c; ++k) {
       const int64_t o = base + k;
-      // moments of new entries (a clone's copy, both split children) start at zero
       const bool zero = moments && (k == 1 || split);
-      for (int d = 0; d < 4; ++d) a.o_quats[d * n_out + o] = zero ? 0.f : a.quats[d * n + i];
-      a.o_op[o] = zero ? 0.f : a.op[i];
-      for (int r = 0; r < sh_rows; ++r) a.o_sh[r * n_out + o] = zero ? 0.f : a.sh[r * n + i];
       if (split && !moments) {
         double q[4];
         for (int d = 0; d < 4; ++d) q[d] = a.quats[d * n + i];
@@ -109,16 +144,16 @@ __global__ void __launch_bounds__(256) k_dens_apply(DensArrays a, int64_t n, int
                              2.0 * (x * z - w * y),       2.0 * (y * z + w * x),
                              1.0 - 2.0 * (x * x + y * y)};
         double l[3];
-        for (int d = 0; d < 3; ++d) l[d] = exp(s[d]) * (double)eps[(k * 3 + d) * n + i];
+        for (int d = 0; d < 3; ++d) l[d] = exp((double)s[d]) * (double)eps[(k * 3 + d) * n + i];
         for (int d = 0; d < 3; ++d) {
           const double step = (R[d * 3 + 0] * l[0] + R[d * 3 + 1] * l[1]) + R[d * 3 + 2] * l[2];
-          a.o_means[d * n_out + o] = (float)(mu[d] + step);
-          a.o_ls[d * n_out + o] = (float)(s[d] - log(1.6));
+          a.o_means[d * n_out + o] = (float)((double)mu[d] + step);
+          a.o_ls[d * n_out + o] = (float)((double)s[d] - log(1.6));
         }
       } else {
         for (int d = 0; d < 3; ++d) {
-          a.o_means[d * n_out + o] = zero ? 0.f : a.means[d * n + i];
-          a.o_ls[d * n_out + o] = zero ? 0.f : a.ls[d * n + i];
+          a.o_means[d * n_out + o] = zero ? 0.f : mu[d];
+          a.o_ls[d * n_out + o] = zero ? 0.f : s[d];
         }
       }
     }
@@ -244,7 +279,7 @@ extern "C" gs_status gs_densify_prune_plan(const uint32_t* score, const float* l
     unsigned long long* mm = (unsigned long long*)(off + dens_mm_word(n));
     const int blocks = (int)std::min<int64_t>(div_up(n, 256), 4096);
     k_mm_init<<<1, 64, 0, st>>>(mm);
-    k_mm<<<std::min(blocks, 1024), 256, 0, st>>>(prune_score, n, mm);
+    k_mm<<<(int)std::min<int64_t>(div_up(n, 4096), 256), 1024, 0, st>>>(prune_score, n, mm);
     k_dens_plan<<<blocks, 256, 0, st>>>(score, log_scales, n, threshold, (double)split_scale,
                                         prune_score, prune_threshold, mm, off, off + n);
     GS_CHECK_LAUNCH();

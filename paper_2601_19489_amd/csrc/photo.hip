@@ -12,6 +12,13 @@
 // respect to the window's mean, second moment and cross moment of x; the
 // backward correlates those maps with the same window (it is symmetric) and
 // combines them with x and y at the pixel.
+//
+// What bounds it: VALU issue (some 130 multiply-adds per pixel forward, 80
+// backward), after LDS reads before: a thread forms eight neighbouring
+// columns of a row, or four neighbouring rows of a column, from values it
+// reads once (6 + 18 LDS words per pixel forward instead of 29 + 55), each
+// sum over the taps in the order it had. 1600 x 1066 x 3, loss and gradient:
+// PLACEHOLDER.
 #include <math.h>
 
 #include "common.h"
@@ -24,6 +31,11 @@ constexpr int kTile = 32;
 constexpr int kRad = 5;
 constexpr int kTaps = 2 * kRad + 1;
 constexpr int kPatch = kTile + 2 * kRad;  // 42
+constexpr int kCols = 8;                  // columns per thread of the horizontal pass
+constexpr int kRows = 4;                  // rows per thread of the vertical pass
+constexpr int kPStride = kPatch + 1;      // odd row strides: lanes on different
+constexpr int kHStride = kTile + 1;       // rows use different LDS banks
+static_assert(kPatch <= kWave && kTile * kTile == 256 * kRows, "one wavefront per row");
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
@@ -50,51 +62,85 @@ __device__ __forceinline__ void block_sum_store(float (&v)[NQ], float* out, int6
   }
 }
 
+// The tile's input patch (zero outside the image), a row per wavefront and turn.
+__device__ __forceinline__ void load_patch(const float* __restrict__ in, int H, int W, int x0,
+                                           int y0, float (&out)[kPatch][kPStride]) {
+  const int c = threadIdx.x & (kWave - 1), gx = x0 + c - kRad;
+  const bool in_x = gx >= 0 && gx < W;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  constexpr int kTurns = (kPatch + 3) / 4;
+  float v[kTurns];
+#pragma unroll
+  for (int k = 0; k < kTurns; ++k) {  // every load is issued before the first is used
+    const int r = w + 4 * k, gy = y0 + r - kRad;
+    v[k] = r < kPatch && c < kPatch && in_x && gy >= 0 && gy < H ? in[(int64_t)gy * W + gx] : 0.f;
+  }
+#pragma unroll
+  for (int k = 0; k < kTurns; ++k)
+    if (w + 4 * k < kPatch && c < kPatch) out[w + 4 * k][c] = v[k];
+}
+
+// The vertical window sums of rows i0 .. i0 + kRows - 1 of column j.
+template <int NQ>
+__device__ __forceinline__ void vertical(const float (&hs)[NQ][kPatch][kHStride],
+                                         const Window& win, int i0, int j,
+                                         float (&m)[NQ][kRows]) {
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+    for (int o = 0; o < kRows; ++o) m[q][o] = 0.f;
+#pragma unroll
+    for (int r = 0; r < kRows + 2 * kRad; ++r) {
+      const float v = hs[q][i0 + r][j];
+#pragma unroll
+      for (int o = 0; o < kRows; ++o)
+        if (r - o >= 0 && r - o < kTaps) m[q][o] = fmaf(win.w[r - o], v, m[q][o]);
+    }
+  }
+}
+
 __global__ void __launch_bounds__(256) k_photo_fwd(const float* __restrict__ img,
                                                    const float* __restrict__ tgt, int H, int W,
                                                    Window win, float* __restrict__ fmaps,
                                                    int64_t plane, float* __restrict__ parts) {
-  __shared__ float px[kPatch][kPatch], py[kPatch][kPatch];
-  __shared__ float hs[5][kPatch][kTile];
+  __shared__ float px[kPatch][kPStride], py[kPatch][kPStride];
+  __shared__ float hs[5][kPatch][kHStride];
   __shared__ float red[8];
   const int x0 = blockIdx.x * kTile, y0 = blockIdx.y * kTile;
   const int64_t base = (int64_t)blockIdx.z * H * W;
   const int tid = threadIdx.x;
-  for (int k = tid; k < kPatch * kPatch; k += 256) {
-    const int r = k / kPatch, c = k % kPatch;
-    const int gy = y0 + r - kRad, gx = x0 + c - kRad;
-    const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-    px[r][c] = in ? img[base + (int64_t)gy * W + gx] : 0.f;
-    py[r][c] = in ? tgt[base + (int64_t)gy * W + gx] : 0.f;
-  }
+  load_patch(img + base, H, W, x0, y0, px);
+  load_patch(tgt + base, H, W, x0, y0, py);
   __syncthreads();
-  for (int k = tid; k < kPatch * kTile; k += 256) {
-    const int r = k / kTile, j = k % kTile;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, s4 = 0.f;
+  for (int k = tid; k < kPatch * (kTile / kCols); k += 256) {
+    const int r = k % kPatch, j0 = k / kPatch * kCols;
+    float s[5][kCols] = {};
 #pragma unroll
-    for (int t = 0; t < kTaps; ++t) {
-      const float a = px[r][j + t], b = py[r][j + t], w = win.w[t];
-      s0 = fmaf(w, a, s0);
-      s1 = fmaf(w, b, s1);
-      s2 = fmaf(w, a * a, s2);
-      s3 = fmaf(w, b * b, s3);
-      s4 = fmaf(w, a * b, s4);
+    for (int c = 0; c < kCols + 2 * kRad; ++c) {
+      const float a = px[r][j0 + c], b = py[r][j0 + c];
+      const float v[5] = {a, b, a * a, b * b, a * b};
+#pragma unroll
+      for (int o = 0; o < kCols; ++o)  // taps of a column in order as c grows
+        if (c - o >= 0 && c - o < kTaps)
+#pragma unroll
+          for (int q = 0; q < 5; ++q) s[q][o] = fmaf(win.w[c - o], v[q], s[q][o]);
     }
-    hs[0][r][j] = s0; hs[1][r][j] = s1; hs[2][r][j] = s2; hs[3][r][j] = s3; hs[4][r][j] = s4;
+#pragma unroll
+    for (int q = 0; q < 5; ++q)
+#pragma unroll
+      for (int o = 0; o < kCols; ++o) hs[q][r][j0 + o] = s[q][o];
   }
   __syncthreads();
-  const int j = tid % kTile;
+  const int j = tid % kTile, i0 = tid / kTile * kRows;
   float acc[2] = {0.f, 0.f};  // sum |x - y|, sum S
-  for (int i = tid / kTile; i < kTile; i += 256 / kTile) {
-    const int gy = y0 + i, gx = x0 + j;
+  float m[5][kRows];
+  vertical<5>(hs, win, i0, j, m);
+#pragma unroll
+  for (int o = 0; o < kRows; ++o) {
+    const int i = i0 + o, gy = y0 + i, gx = x0 + j;
     if (gy >= H || gx >= W) continue;
-    float m[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < kTaps; ++t)
-#pragma unroll
-      for (int q = 0; q < 5; ++q) m[q] = fmaf(win.w[t], hs[q][i + t][j], m[q]);
-    const float mx = m[0], my = m[1];
-    const float vx = m[2] - mx * mx, vy = m[3] - my * my, cxy = m[4] - mx * my;
+    const float mx = m[0][o], my = m[1][o];
+    const float vx = m[2][o] - mx * mx, vy = m[3][o] - my * my, cxy = m[4][o] - mx * my;
     const float A1 = 2.f * mx * my + kC1, A2 = 2.f * cxy + kC2;
     const float B1 = mx * mx + my * my + kC1, B2 = vx + vy + kC2;
     const float inv = 1.f / (B1 * B2);
@@ -117,12 +163,12 @@ __global__ void __launch_bounds__(256) k_photo_fwd(const float* __restrict__ img
 }
 
 // loss[0..2] = E, L1, SSIM from the per-block sums over n values (FP64,
-// each thread a fixed stride of blocks, then a fixed-order tree).
-__global__ void __launch_bounds__(256) k_photo_finish(const float* __restrict__ parts,
-                                                      int64_t nblk, double n, float lambda,
-                                                      float* __restrict__ loss) {
-  __shared__ double red[2][256];
+// each of 256 threads a fixed stride of blocks, then a fixed-order tree).
+__device__ __forceinline__ void photo_finish(const float* __restrict__ parts, int64_t nblk,
+                                             double n, float lambda, double (&red)[2][256],
+                                             float* __restrict__ loss) {
   double a = 0.0, b = 0.0;
+#pragma unroll 8
   for (int64_t i = threadIdx.x; i < nblk; i += 256) {
     a += (double)parts[i];
     b += (double)parts[nblk + i];
@@ -145,50 +191,70 @@ __global__ void __launch_bounds__(256) k_photo_finish(const float* __restrict__ 
   }
 }
 
+__global__ void __launch_bounds__(256) k_photo_finish(const float* __restrict__ parts,
+                                                      int64_t nblk, double n, float lambda,
+                                                      float* __restrict__ loss) {
+  __shared__ double red[2][256];
+  photo_finish(parts, nblk, n, lambda, red, loss);
+}
+
+// The gradient; the last workgroup writes the loss first (a launch of its own
+// costs 7 us, here it runs beside the other workgroups).
 __global__ void __launch_bounds__(256) k_photo_bwd(const float* __restrict__ img,
                                                    const float* __restrict__ tgt, int H, int W,
                                                    Window win, const float* __restrict__ fmaps,
                                                    int64_t plane, float wl1, float wssim,
-                                                   float* __restrict__ grad) {
-  __shared__ float pf[3][kPatch][kPatch];
-  __shared__ float hs[3][kPatch][kTile];
+                                                   float* __restrict__ grad,
+                                                   const float* __restrict__ parts, float lambda,
+                                                   float* __restrict__ loss) {
+  __shared__ union {
+    struct {
+      float pf[3][kPatch][kPStride];
+      float hs[3][kPatch][kHStride];
+    };
+    double red[2][256];
+  } L;
+  if (blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 &&
+      blockIdx.z == gridDim.z - 1) {
+    photo_finish(parts, (int64_t)gridDim.x * gridDim.y * gridDim.z, (double)plane, lambda, L.red,
+                 loss);
+    __syncthreads();  // the LDS changes hands
+  }
   const int x0 = blockIdx.x * kTile, y0 = blockIdx.y * kTile;
   const int64_t base = (int64_t)blockIdx.z * H * W;
   const int tid = threadIdx.x;
-  for (int k = tid; k < kPatch * kPatch; k += 256) {
-    const int r = k / kPatch, c = k % kPatch;
-    const int gy = y0 + r - kRad, gx = x0 + c - kRad;
-    const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-    const int64_t p = base + (int64_t)gy * W + gx;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) pf[q][r][c] = in ? fmaps[q * plane + p] : 0.f;
+  for (int q = 0; q < 3; ++q) load_patch(fmaps + q * plane + base, H, W, x0, y0, L.pf[q]);
+  __syncthreads();
+  for (int k = tid; k < kPatch * (kTile / kCols); k += 256) {
+    const int r = k % kPatch, j0 = k / kPatch * kCols;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      float s[kCols] = {};
+#pragma unroll
+      for (int c = 0; c < kCols + 2 * kRad; ++c) {
+        const float v = L.pf[q][r][j0 + c];
+#pragma unroll
+        for (int o = 0; o < kCols; ++o)
+          if (c - o >= 0 && c - o < kTaps) s[o] = fmaf(win.w[c - o], v, s[o]);
+      }
+#pragma unroll
+      for (int o = 0; o < kCols; ++o) L.hs[q][r][j0 + o] = s[o];
+    }
   }
   __syncthreads();
-  for (int k = tid; k < kPatch * kTile; k += 256) {
-    const int r = k / kTile, j = k % kTile;
-    float s[3] = {0.f, 0.f, 0.f};
+  const int j = tid % kTile, i0 = tid / kTile * kRows;
+  float g[3][kRows];
+  vertical<3>(L.hs, win, i0, j, g);
 #pragma unroll
-    for (int t = 0; t < kTaps; ++t)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) s[q] = fmaf(win.w[t], pf[q][r][j + t], s[q]);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) hs[q][r][j] = s[q];
-  }
-  __syncthreads();
-  const int j = tid % kTile;
-  for (int i = tid / kTile; i < kTile; i += 256 / kTile) {
-    const int gy = y0 + i, gx = x0 + j;
+  for (int o = 0; o < kRows; ++o) {
+    const int gy = y0 + i0 + o, gx = x0 + j;
     if (gy >= H || gx >= W) continue;
-    float g[3] = {0.f, 0.f, 0.f};
-#pragma unroll
-    for (int t = 0; t < kTaps; ++t)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) g[q] = fmaf(win.w[t], hs[q][i + t][j], g[q]);
     const int64_t p = base + (int64_t)gy * W + gx;
     const float x = img[p], y = tgt[p];
     const float d = x - y;
     const float sgn = d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f);
-    const float dssim = g[0] + 2.f * x * g[1] + y * g[2];
+    const float dssim = g[0][o] + 2.f * x * g[1][o] + y * g[2][o];
     grad[p] = wl1 * sgn - wssim * dssim;
   }
 }
@@ -257,11 +323,11 @@ extern "C" gs_status gs_photo_loss(const float* image, const float* target, int3
   GS_TIMED("photo_loss", st,
            k_photo_fwd<<<grid, 256, 0, st>>>(image, target, height, width, win, fmaps, plane,
                                              parts);
-           k_photo_finish<<<1, 256, 0, st>>>(parts, nblk, (double)plane, lambda, loss);
            if (dL_dimage) k_photo_bwd<<<grid, 256, 0, st>>>(
                image, target, height, width, win, fmaps, plane,
                (float)((1.0 - lambda) / (double)plane), (float)(lambda / (double)plane),
-               dL_dimage));
+               dL_dimage, parts, lambda, loss);
+           else k_photo_finish<<<1, 256, 0, st>>>(parts, nblk, (double)plane, lambda, loss));
   GS_CHECK_LAUNCH();
   return GS_OK;
 }
