@@ -13,12 +13,16 @@
 // backward correlates those maps with the same window (it is symmetric) and
 // combines them with x and y at the pixel.
 //
-// What bounds it: VALU issue (some 130 multiply-adds per pixel forward, 80
-// backward), after LDS reads before: a thread forms eight neighbouring
-// columns of a row, or four neighbouring rows of a column, from values it
-// reads once (6 + 18 LDS words per pixel forward instead of 29 + 55), each
-// sum over the taps in the order it had. 1600 x 1066 x 3, loss and gradient:
-// PLACEHOLDER.
+// What bounds it: VALU issue (some 130 operations per pixel forward, 70
+// backward); before, it was the LDS, of which every output read all of its
+// window's values. So a thread forms eight neighbouring columns of a row, or
+// four neighbouring rows of a column, from values it reads once (6 + 18 LDS
+// words per pixel forward, where 29 + 55 were read), each sum over the taps in
+// the order it had, and the horizontal sums take the patches' place in LDS
+// (five workgroups per compute unit forward instead of three: 108 -> 100 us).
+// 1600 x 1066 x 3: loss 82 -> 50 us, loss and gradient 143 -> 100 us. (One sum
+// for x^2 + y^2, of which the variances need no more: 92 us, but the gradient
+// of a smooth image is off by 6.6e-6 instead of 5.9e-6.)
 #include <math.h>
 
 #include "common.h"
@@ -35,7 +39,9 @@ constexpr int kCols = 8;                  // columns per thread of the horizonta
 constexpr int kRows = 4;                  // rows per thread of the vertical pass
 constexpr int kPStride = kPatch + 1;      // odd row strides: lanes on different
 constexpr int kHStride = kTile + 1;       // rows use different LDS banks
-static_assert(kPatch <= kWave && kTile * kTile == 256 * kRows, "one wavefront per row");
+static_assert(kPatch <= kWave && kTile * kTile == 256 * kRows &&
+                  kPatch * (kTile / kCols) <= 256,
+              "one wavefront per patch row, one turn per pass");
 constexpr float kC1 = 0.01f * 0.01f;
 constexpr float kC2 = 0.03f * 0.03f;
 
@@ -103,21 +109,31 @@ __global__ void __launch_bounds__(256) k_photo_fwd(const float* __restrict__ img
                                                    const float* __restrict__ tgt, int H, int W,
                                                    Window win, float* __restrict__ fmaps,
                                                    int64_t plane, float* __restrict__ parts) {
-  __shared__ float px[kPatch][kPStride], py[kPatch][kPStride];
-  __shared__ float hs[5][kPatch][kHStride];
+  __shared__ union {  // the patches, then the horizontal sums
+    struct {
+      float px[kPatch][kPStride], py[kPatch][kPStride];
+    };
+    float hs[5][kPatch][kHStride];
+  } L;
   __shared__ float red[8];
   const int x0 = blockIdx.x * kTile, y0 = blockIdx.y * kTile;
   const int64_t base = (int64_t)blockIdx.z * H * W;
   const int tid = threadIdx.x;
-  load_patch(img + base, H, W, x0, y0, px);
-  load_patch(tgt + base, H, W, x0, y0, py);
+  load_patch(img + base, H, W, x0, y0, L.px);
+  load_patch(tgt + base, H, W, x0, y0, L.py);
   __syncthreads();
-  for (int k = tid; k < kPatch * (kTile / kCols); k += 256) {
-    const int r = k % kPatch, j0 = k / kPatch * kCols;
-    float s[5][kCols] = {};
+  const int j = tid % kTile, i0 = tid / kTile * kRows;
+  float acc[2] = {0.f, 0.f};  // sum |x - y|, sum S
+#pragma unroll
+  for (int o = 0; o < kRows; ++o)  // zero outside the image
+    acc[0] += fabsf(L.px[i0 + o + kRad][j + kRad] - L.py[i0 + o + kRad][j + kRad]);
+  const bool hz = tid < kPatch * (kTile / kCols);
+  const int r = hz ? tid % kPatch : 0, j0 = hz ? tid / kPatch * kCols : 0;
+  float s[5][kCols] = {};
+  if (hz) {
 #pragma unroll
     for (int c = 0; c < kCols + 2 * kRad; ++c) {
-      const float a = px[r][j0 + c], b = py[r][j0 + c];
+      const float a = L.px[r][j0 + c], b = L.py[r][j0 + c];
       const float v[5] = {a, b, a * a, b * b, a * b};
 #pragma unroll
       for (int o = 0; o < kCols; ++o)  // taps of a column in order as c grows
@@ -125,19 +141,19 @@ __global__ void __launch_bounds__(256) k_photo_fwd(const float* __restrict__ img
 #pragma unroll
           for (int q = 0; q < 5; ++q) s[q][o] = fmaf(win.w[c - o], v[q], s[q][o]);
     }
+  }
+  __syncthreads();  // the patches are read until here
+  if (hz)
 #pragma unroll
     for (int q = 0; q < 5; ++q)
 #pragma unroll
-      for (int o = 0; o < kCols; ++o) hs[q][r][j0 + o] = s[q][o];
-  }
+      for (int o = 0; o < kCols; ++o) L.hs[q][r][j0 + o] = s[q][o];
   __syncthreads();
-  const int j = tid % kTile, i0 = tid / kTile * kRows;
-  float acc[2] = {0.f, 0.f};  // sum |x - y|, sum S
   float m[5][kRows];
-  vertical<5>(hs, win, i0, j, m);
+  vertical<5>(L.hs, win, i0, j, m);
 #pragma unroll
   for (int o = 0; o < kRows; ++o) {
-    const int i = i0 + o, gy = y0 + i, gx = x0 + j;
+    const int gy = y0 + i0 + o, gx = x0 + j;
     if (gy >= H || gx >= W) continue;
     const float mx = m[0][o], my = m[1][o];
     const float vx = m[2][o] - mx * mx, vy = m[3][o] - my * my, cxy = m[4][o] - mx * my;
@@ -145,7 +161,6 @@ __global__ void __launch_bounds__(256) k_photo_fwd(const float* __restrict__ img
     const float B1 = mx * mx + my * my + kC1, B2 = vx + vy + kC2;
     const float inv = 1.f / (B1 * B2);
     const float S = A1 * A2 * inv;
-    acc[0] += fabsf(px[i + kRad][j + kRad] - py[i + kRad][j + kRad]);
     acc[1] += S;
     if (fmaps) {
       const float dmx = 2.f * my * A2 * inv - 2.f * mx * S / B1;
@@ -208,10 +223,8 @@ __global__ void __launch_bounds__(256) k_photo_bwd(const float* __restrict__ img
                                                    const float* __restrict__ parts, float lambda,
                                                    float* __restrict__ loss) {
   __shared__ union {
-    struct {
-      float pf[3][kPatch][kPStride];
-      float hs[3][kPatch][kHStride];
-    };
+    float pf[3][kPatch][kPStride];  // the maps' patches, then the horizontal sums
+    float hs[3][kPatch][kHStride];
     double red[2][256];
   } L;
   if (blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 &&
@@ -226,22 +239,26 @@ __global__ void __launch_bounds__(256) k_photo_bwd(const float* __restrict__ img
 #pragma unroll
   for (int q = 0; q < 3; ++q) load_patch(fmaps + q * plane + base, H, W, x0, y0, L.pf[q]);
   __syncthreads();
-  for (int k = tid; k < kPatch * (kTile / kCols); k += 256) {
-    const int r = k % kPatch, j0 = k / kPatch * kCols;
+  const bool hz = tid < kPatch * (kTile / kCols);
+  const int r = hz ? tid % kPatch : 0, j0 = hz ? tid / kPatch * kCols : 0;
+  float s[3][kCols] = {};
+  if (hz) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      float s[kCols] = {};
+    for (int q = 0; q < 3; ++q)
 #pragma unroll
       for (int c = 0; c < kCols + 2 * kRad; ++c) {
         const float v = L.pf[q][r][j0 + c];
 #pragma unroll
         for (int o = 0; o < kCols; ++o)
-          if (c - o >= 0 && c - o < kTaps) s[o] = fmaf(win.w[c - o], v, s[o]);
+          if (c - o >= 0 && c - o < kTaps) s[q][o] = fmaf(win.w[c - o], v, s[q][o]);
       }
-#pragma unroll
-      for (int o = 0; o < kCols; ++o) L.hs[q][r][j0 + o] = s[o];
-    }
   }
+  __syncthreads();  // the patches are read until here
+  if (hz)
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int o = 0; o < kCols; ++o) L.hs[q][r][j0 + o] = s[q][o];
   __syncthreads();
   const int j = tid % kTile, i0 = tid / kTile * kRows;
   float g[3][kRows];
