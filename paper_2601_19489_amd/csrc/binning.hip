@@ -51,7 +51,7 @@ struct BinLayout {
   int64_t dkA, dkB, dvA, dvB, spA, spB, ptot;
   int64_t runs, colh;
   int64_t cstart, nseg, segfirst, misc, hist, segtot;
-  int64_t rtmp, stmp, total;
+  int64_t rtmp, stmp, rgrp, total;
   int64_t ns_max, nblk;
 };
 
@@ -83,6 +83,7 @@ BinLayout layout(int64_t n, int64_t cap, int tiles_x, int tiles_y) {
   L.segtot = o; o += al(4 * L.ns_max);
   L.rtmp = o; o += al(4 * radix_tmp_words(std::max<int64_t>(n, 1)));
   L.stmp = o; o += al(4 * (scan_tmp_words(std::max<int64_t>(ncolh, 1)) + 1));
+  L.rgrp = o; o += al(4 * 4 * radix_group_words(n));  // four passes
   L.total = o;
   return L;
 }
@@ -97,14 +98,18 @@ __device__ __forceinline__ uint64_t pair_total(const uint32_t* misc) {
 }
 
 // partial sums of the tile counts, one per workgroup (64-bit, so an overflow
-// of the capacity is always seen); k_seg_layout adds them up
+// of the capacity is always seen); k_seg_layout adds them up. Also clears the
+// sort's group counts.
 __global__ void __launch_bounds__(256) k_count_partials(const uint32_t* __restrict__ counts,
                                                         int64_t n,
-                                                        unsigned long long* __restrict__ part) {
+                                                        unsigned long long* __restrict__ part,
+                                                        uint32_t* __restrict__ zero,
+                                                        int64_t n_zero) {
   __shared__ unsigned long long wp[256 / kWave];
   unsigned long long acc = 0;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t k = i; k < n_zero; k += stride) zero[k] = 0u;
   // four loads in flight per thread
   for (; i + 3 * stride < n; i += 4 * stride) {
     const uint32_t c0 = counts[i], c1 = counts[i + stride], c2 = counts[i + 2 * stride],
@@ -469,10 +474,12 @@ __global__ void __launch_bounds__(kScanThreads1) k_col_scan(
     if (tx == tiles_x - 1 && threadIdx.x == 0) ranges[n_tiles] = 0;
     return;
   }
-  const int G = NTH / tiles_y;  // >= 4 groups (tiles_y <= 256)
+  const uint32_t ns = nseg[tx], sf = segfirst[tx];
+  // at least 4 groups fit (tiles_y <= 256); no more than there are segments,
+  // since the groups are summed one after the other
+  const int G = (int)max(min((uint32_t)(NTH / tiles_y), ns), 1u);
   const int ty = threadIdx.x % tiles_y, g = threadIdx.x / tiles_y;
   const bool act = g < G;
-  const uint32_t ns = nseg[tx], sf = segfirst[tx];
   // the pairs of the earlier columns: the totals of the segments before sf
   uint32_t part = 0;
   uint32_t t = threadIdx.x;
@@ -729,7 +736,8 @@ static gs_status bin_sort(const float* splats, const uint32_t* depth_keys,
   uint32_t* colh = U(L.colh);
   const int64_t ncolh = (int64_t)cd.tiles_x * L.nblk;
   if (n > 0) {
-    k_count_partials<<<nparts, 256, 0, st>>>(tile_counts, n, part);
+    const int64_t ngw = radix_group_words(n);
+    k_count_partials<<<nparts, 256, 0, st>>>(tile_counts, n, part, U(L.rgrp), 4 * ngw);
     GS_CHECK_LAUNCH();
     // 1. stable depth sort (Gaussians without tiles carry 0xFFFFFFFF); the
     // first pass takes the Gaussian indices as its values and each
@@ -744,7 +752,8 @@ static gs_status bin_sort(const float* splats, const uint32_t* depth_keys,
                                      : (even ? sA : sB);
       s = radix_pass(kin, pass == 0 ? nullptr : (even ? vA : vB), even ? kB : kA, even ? vB : vA,
                      n, nullptr, pass * 8, U(L.rtmp), st, s2, even ? sB : sA, 8,
-                     pass == 0 ? GS_SPLAT_FLOATS : 1);
+                     pass == 0 ? GS_SPLAT_FLOATS : 1,
+                     ngw > 0 ? U(L.rgrp) + pass * ngw : nullptr);
       if (s != GS_OK) return s;
       kin = even ? kB : kA;
     }

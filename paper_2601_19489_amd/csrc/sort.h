@@ -25,8 +25,11 @@ int64_t scan_tmp_words(int64_t n);
 gs_status scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total, uint32_t* tmp,
                    hipStream_t st, const uint32_t* n_dev = nullptr, int in_shift = 0);
 
-// Words of temporary storage one radix pass needs for up to n keys.
+// Words of temporary storage one radix pass needs for up to n keys, and of
+// the group counts that a pass in two launches takes zeroed (0 words: the
+// passes over that many keys take none).
 int64_t radix_tmp_words(int64_t n);
+int64_t radix_group_words(int64_t n);
 
 // One stable counting pass on digit (key >> shift) & 255 over the first
 // count keys, where count = *n_dev if n_dev is not null, else n_max; if
@@ -35,16 +38,13 @@ int64_t radix_tmp_words(int64_t n);
 // second value array (vals2_in/out) is carried when given. bits (1..8): the
 // digit bits that can be set in any key (a cheaper ranking below 8).
 // vals2_in is read with a stride of vals2_stride words (1: contiguous).
+// groups: radix_group_words(n_max) zeroed words, used by this pass alone
+// (where that is not 0, n_dev has to be null).
 gs_status radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out,
                      uint32_t* vals_out, int64_t n_max, const uint32_t* n_dev, int shift,
                      uint32_t* tmp, hipStream_t st, const uint32_t* vals2_in = nullptr,
-                     uint32_t* vals2_out = nullptr, int bits = 8, int vals2_stride = 1);
-
-// Keys per tile of a radix pass over up to n_max keys. After a pass, tmp
-// holds its scanned histogram laid out [digit][tile] over the
-// ceil(count / tile) live tiles: word d * tiles is the first output position
-// of digit d.
-int64_t radix_tile_keys(int64_t n_max);
+                     uint32_t* vals2_out = nullptr, int bits = 8, int vals2_stride = 1,
+                     uint32_t* groups = nullptr);
 
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
   const int lane = threadIdx.x & (kWave - 1);

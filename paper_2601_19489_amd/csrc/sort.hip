@@ -6,8 +6,10 @@
 // Scan: reduce each tile to its sum, then scan each tile from its offset,
 // which its workgroup sums from the earlier tiles' sums itself (input read
 // twice, two launches at any size).
+// An array of at most kScanOne words is scanned by one workgroup instead.
 // Radix pass: per-tile digit histogram laid out [digit][live tile], scanned,
-// then each tile's keys are ranked stably and scattered.
+// then each tile's keys are ranked stably and scattered. Up to 2^22 keys the
+// scan is left out: see k_radix_count.
 #include "sort.h"
 
 namespace gs {
@@ -103,6 +105,32 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_chunks(const uint32_t* in
   }
 }
 
+// The whole scan by one workgroup, two launches fewer in a row of small ones
+// (4.5 us each, whatever they do): 16 words per thread at most.
+constexpr int kScanOne = 1024 * kScanItems;
+__global__ void __launch_bounds__(1024) k_scan_one(const uint32_t* in, uint32_t* out, int n,
+                                                   const uint32_t* n_dev, int in_shift,
+                                                   uint32_t* total) {
+  __shared__ uint32_t wsum[1024 / kWave];
+  const int count = (int)eff_count(n, n_dev);
+  const int per = (count + 1023) / 1024;  // consecutive words per thread
+  const int lo = threadIdx.x * per;
+  uint32_t v[kScanItems], s = 0;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    v[k] = k < per && lo + k < count ? in[lo + k] >> in_shift : 0u;
+    s += v[k];
+  }
+  uint32_t tot;
+  uint32_t run = block_exclusive_scan<1024>(s, wsum, tot);
+  if (threadIdx.x == 0 && total) *total = tot;
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) {
+    if (k < per && lo + k < count) out[lo + k] = run;
+    run += v[k];
+  }
+}
+
 __global__ void k_set_u32(uint32_t* p, uint32_t v) { *p = v; }
 
 int64_t scan_tmp_words(int64_t n) { return (n + kScanTile - 1) / kScanTile + 1; }
@@ -114,6 +142,11 @@ gs_status scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total
       k_set_u32<<<1, 1, 0, st>>>(total, 0u);
       GS_CHECK_LAUNCH();
     }
+    return GS_OK;
+  }
+  if (n <= kScanOne) {
+    k_scan_one<<<1, 1024, 0, st>>>(in, out, (int)n, n_dev, in_shift, total);
+    GS_CHECK_LAUNCH();
     return GS_OK;
   }
   const int64_t tiles = (n + kScanTile - 1) / kScanTile;
@@ -133,8 +166,8 @@ __device__ __forceinline__ int64_t sort_count(int64_t n_max, const uint32_t* n_d
 }
 
 // Keys per thread of a radix tile: small tiles for short arrays (enough
-// workgroups to fill the chip), long ones for long arrays (less fixed work
-// per key).
+// workgroups to fill the chip, and the pass in two launches), long ones for
+// long arrays (less fixed work per key, and the pass in four).
 static int sort_items(int64_t n_max) { return n_max <= ((int64_t)1 << 22) ? 8 : 16; }
 
 template <int ITEMS>
@@ -177,6 +210,59 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_hist(const uint32_t* __r
   }
 }
 
+// The pass in two launches, for arrays of at most kGridMax tiles: each tile's
+// histogram goes to hist[tile][digit] and is added to its group's, 32 tiles to
+// a group, and a tile's first position of a digit is then summed up by the
+// tile's own workgroup of k_radix_scatter: the groups before its own, the
+// tiles before it in its group, and the lower digits' totals (at most 64 + 31
+// coalesced loads per thread). Against the histogram, a scan in two launches
+// and the scatter, per pass: 28.7 -> 22.9 us at
+// 1M keys (the scatter itself 14.2 -> 17.7), and two launches of 4.5 us fewer
+// for short arrays.
+constexpr int kRadixGroup = 32;
+__global__ void __launch_bounds__(kSortThreads) k_radix_count(const uint32_t* __restrict__ keys,
+                                                              int64_t n, int shift,
+                                                              uint32_t* __restrict__ hist,
+                                                              uint32_t* __restrict__ groups) {
+  constexpr int ITEMS = 8;
+  __shared__ uint32_t h[kRadixBins];
+  const int64_t lo = (int64_t)blockIdx.x * kSortThreads * ITEMS;
+  // all of the thread's loads are issued before the first is used
+  uint32_t k[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t i = lo + threadIdx.x + (int64_t)r * kSortThreads;
+    k[r] = keys[i < n ? i : lo];
+  }
+  h[threadIdx.x] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r)
+    if (lo + threadIdx.x + (int64_t)r * kSortThreads < n)
+      atomicAdd(&h[(k[r] >> shift) & (kRadixBins - 1)], 1u);
+  __syncthreads();
+  const uint32_t c = h[threadIdx.x];
+  hist[(int64_t)blockIdx.x * kRadixBins + threadIdx.x] = c;
+  if (c) atomicAdd(&groups[(blockIdx.x / kRadixGroup) * kRadixBins + threadIdx.x], c);
+}
+
+// The first position of digit threadIdx.x in tile `tile` of the nb.
+__device__ __forceinline__ uint32_t radix_base(const uint32_t* __restrict__ hist,
+                                               const uint32_t* __restrict__ groups, int tile,
+                                               int nb, uint32_t* wsum) {
+  const int g0 = tile / kRadixGroup, ng = (nb + kRadixGroup - 1) / kRadixGroup;
+  uint32_t before = 0, total = 0, all;
+#pragma unroll 8
+  for (int g = 0; g < ng; ++g) {
+    const uint32_t c = groups[g * kRadixBins + threadIdx.x];
+    total += c;
+    before += g < g0 ? c : 0u;
+  }
+#pragma unroll 8
+  for (int t = g0 * kRadixGroup; t < tile; ++t) before += hist[t * kRadixBins + threadIdx.x];
+  return block_exclusive_scan<kSortThreads>(total, wsum, all) + before;
+}
+
 // Stable scatter, one tile of 256 * ITEMS keys at a time. Wave w owns the
 // contiguous segment [w * 64 * ITEMS, (w + 1) * 64 * ITEMS) of the tile and
 // walks it in ITEMS rounds of 64 in order; lanes holding the same digit in a
@@ -193,7 +279,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_scatter(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t n_max,
     const uint32_t* __restrict__ n_dev, int shift, const uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ vals2_in, uint32_t* __restrict__ vals2_out, int bits,
+    const uint32_t* __restrict__ groups, const uint32_t* __restrict__ vals2_in, uint32_t* __restrict__ vals2_out, int bits,
     int vals2_stride) {
   constexpr int NW = kSortThreads / kWave;
   constexpr int T = kSortThreads * ITEMS;
@@ -215,7 +301,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_scatter(
     // every load of the tile is issued before the ranking uses the first
     // (out-of-range slots read the tile's first key and are masked below);
     // this thread's digit base for the tile is fetched alongside
-    const uint32_t gb = hist[(int64_t)threadIdx.x * nb + tile];
+    uint32_t gb = groups ? 0u : hist[(int64_t)threadIdx.x * nb + tile];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
       const int li = seg + r * kWave + lane;
@@ -224,6 +310,7 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_scatter(
       val[r] = vals_in ? vals_in[idx] : (uint32_t)idx;  // null: the index
       val2[r] = vals2_in ? vals2_in[idx * vals2_stride] : 0u;
     }
+    if (groups) gb = radix_base(hist, groups, (int)tile, (int)nb, wsum);
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
       const int li = seg + r * kWave + lane;
@@ -292,27 +379,42 @@ int64_t radix_tmp_words(int64_t n) {
   return nb * kRadixBins + scan_tmp_words(nb * kRadixBins) + 1;
 }
 
+int64_t radix_group_words(int64_t n) {
+  if (sort_items(n) != 8) return 0;
+  constexpr int64_t T = (int64_t)kSortThreads * 8 * kRadixGroup;
+  return (n + T - 1) / T * kRadixBins;
+}
+
 template <int ITEMS>
 static gs_status radix_pass_t(const uint32_t* keys_in, const uint32_t* vals_in,
                               uint32_t* keys_out, uint32_t* vals_out, int64_t n_max,
                               const uint32_t* n_dev, int shift, uint32_t* tmp, hipStream_t st,
                               const uint32_t* vals2_in, uint32_t* vals2_out, int bits,
-                              int vals2_stride) {
+                              int vals2_stride, uint32_t* groups) {
   constexpr int64_t T = (int64_t)kSortThreads * ITEMS;
   const int64_t nb = (n_max + T - 1) / T;
   const unsigned g = (unsigned)(nb < kGridMax ? nb : kGridMax);
   uint32_t* hist = tmp;
-  uint32_t* scan_n = tmp + nb * kRadixBins + scan_tmp_words(nb * kRadixBins);
-  GS_TIMED("radix_hist", st,
-           k_radix_hist<ITEMS><<<g, kSortThreads, 0, st>>>(keys_in, n_max, n_dev, shift, hist,
-                                                           scan_n));
-  GS_CHECK_LAUNCH();
-  gs_status s = scan_u32(hist, hist, nb * kRadixBins, nullptr, tmp + nb * kRadixBins, st, scan_n);
-  if (s != GS_OK) return s;
+  if constexpr (ITEMS == 8) {
+    static_assert(((int64_t)1 << 22) / T <= kGridMax, "one tile per workgroup");
+    if (!groups || n_dev) return GS_EINVAL;
+    GS_TIMED("radix_hist", st,
+             k_radix_count<<<g, kSortThreads, 0, st>>>(keys_in, n_max, shift, hist, groups));
+    GS_CHECK_LAUNCH();
+  } else {
+    uint32_t* scan_n = tmp + nb * kRadixBins + scan_tmp_words(nb * kRadixBins);
+    GS_TIMED("radix_hist", st,
+             k_radix_hist<ITEMS><<<g, kSortThreads, 0, st>>>(keys_in, n_max, n_dev, shift, hist,
+                                                             scan_n));
+    GS_CHECK_LAUNCH();
+    gs_status s =
+        scan_u32(hist, hist, nb * kRadixBins, nullptr, tmp + nb * kRadixBins, st, scan_n);
+    if (s != GS_OK) return s;
+  }
   GS_TIMED("radix_scatter", st,
            k_radix_scatter<ITEMS><<<g, kSortThreads, 0, st>>>(keys_in, vals_in, keys_out,
                                                               vals_out, n_max, n_dev, shift, hist,
-                                                              vals2_in, vals2_out, bits,
+                                                              groups, vals2_in, vals2_out, bits,
                                                               vals2_stride));
   GS_CHECK_LAUNCH();
   return GS_OK;
@@ -321,16 +423,14 @@ static gs_status radix_pass_t(const uint32_t* keys_in, const uint32_t* vals_in,
 gs_status radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out,
                      uint32_t* vals_out, int64_t n_max, const uint32_t* n_dev, int shift,
                      uint32_t* tmp, hipStream_t st, const uint32_t* vals2_in,
-                     uint32_t* vals2_out, int bits, int vals2_stride) {
+                     uint32_t* vals2_out, int bits, int vals2_stride, uint32_t* groups) {
   if (n_max <= 0) return GS_OK;
   if (bits < 1 || bits > kRadixBits || vals2_stride < 1) return GS_EINVAL;
   if (sort_items(n_max) == 8)
     return radix_pass_t<8>(keys_in, vals_in, keys_out, vals_out, n_max, n_dev, shift, tmp, st,
-                           vals2_in, vals2_out, bits, vals2_stride);
+                           vals2_in, vals2_out, bits, vals2_stride, groups);
   return radix_pass_t<16>(keys_in, vals_in, keys_out, vals_out, n_max, n_dev, shift, tmp, st,
-                          vals2_in, vals2_out, bits, vals2_stride);
+                          vals2_in, vals2_out, bits, vals2_stride, nullptr);
 }
-
-int64_t radix_tile_keys(int64_t n_max) { return (int64_t)kSortThreads * sort_items(n_max); }
 
 }  // namespace gs
