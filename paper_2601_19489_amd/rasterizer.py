@@ -96,6 +96,7 @@ class Rasterizer:
         self.keys_out = None
         self.generation = 0
         self.pairs = None      # pair count of the last checked binning
+        self._pairs_host = None  # pinned, from the first checked forward on
         self._alloc_pairs(max(int(capacity), 1))
 
     def _alloc_pairs(self, capacity):
@@ -135,6 +136,9 @@ class Rasterizer:
 
     def render_fwd(self):
         self.generation += 1
+        self._render()
+
+    def _render(self):
         if self.deferred:
             _lib.gs_render_fwd_deferred(self.splats, self.n, self.workspace, self.capacity,
                                         self.vals, self.ranges, self.cam, self.bg, self.image,
@@ -145,8 +149,31 @@ class Rasterizer:
 
     def forward(self, p, check_overflow: bool = True):
         self.preprocess(p)
-        self.bin_sort(check_overflow=check_overflow)
+        if not check_overflow:
+            self.bin_sort(check_overflow=False)
+            self.render_fwd()
+            return self.image, self.depth
+        # The pair count is read while the forward already runs (on an overflow
+        # every tile is empty, and the forward is run again): reading it first
+        # left the GPU idle for about 35 us of every call.
+        self.generation += 1
+        self.pairs = None
+        self._bin(None)
+        if self._pairs_host is None:
+            self._pairs_host = torch.empty(1, dtype=torch.int32, pin_memory=True)
+        self._pairs_host.copy_(self.pair_count, non_blocking=True)
+        counted = torch.cuda.Event()
+        counted.record(torch.cuda.current_stream(self.device))
         self.render_fwd()
+        counted.synchronize()
+        P = int(self._pairs_host[0]) & 0xFFFFFFFF
+        if P > self.capacity:
+            # the buffers given up below may belong to another stream
+            torch.cuda.current_stream(self.device).synchronize()
+            self._alloc_pairs(int(P * self.headroom) + 1024)
+            self._bin(None)
+            self._render()
+        self.pairs = P
         return self.image, self.depth
 
     def frame(self) -> Frame:
