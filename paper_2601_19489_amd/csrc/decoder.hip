@@ -36,7 +36,6 @@ constexpr int kHid = 32;                   // hidden units per head
 constexpr int kHidAll = 3 * kHid;          // 96
 constexpr int kOut = 110;                  // 10 + 30 + 70 outputs
 constexpr int kTile = 64;                  // anchors per workgroup iteration
-constexpr int kThreads = 256;
 // LDS row strides (elements): BF16 inputs and hidden units, FP32 outputs
 constexpr int kXS = 72, kHS = 104, kYS = 161, kZS = 97, kDS = 65;
 // Padded output columns: head h occupies columns 32 h .. 32 h + 31 (op,
@@ -47,8 +46,12 @@ __host__ __device__ constexpr int head_row(int h) {
   return h == 0 ? 0 : h == 1 ? 10 : h == 2 ? 40 : 110;
 }
 __host__ __device__ constexpr int head_len(int h) { return head_row(h + 1) - head_row(h); }
-__host__ __device__ constexpr int head_fwd_tiles(int h) { return h == 0 ? 1 : h == 1 ? 2 : 5; }
 __host__ __device__ constexpr int head_k_steps(int h) { return h == 2 ? 3 : 1; }
+// The 50 padding columns: 10 .. 31, 62, 63, 134 .. 159.
+__host__ __device__ constexpr int pad_col(int p) {
+  return p < 22 ? 10 + p : p < 24 ? 62 + (p - 22) : 134 + (p - 24);
+}
+constexpr int kBwdThreads = 512;           // the backward's workgroup
 // Per-workgroup partial sums in the workspace: dW1 [96][48], dW2 [160][32]
 // (padded rows), db1 [96], db2 [160].
 constexpr int kWsW1 = 0, kWsW2 = kWsW1 + kHidAll * 48, kWsB1 = kWsW2 + 160 * kHid,
@@ -58,11 +61,15 @@ constexpr int kMaxBlocks = 256;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t f2bf(float f) {  // round to nearest even
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// Round to nearest even: two values in one v_cvt_pk_bf16_f32, the first in the
+// low half.
+__device__ __forceinline__ uint32_t f2bf2(float a, float b) {
+  const bf16x2 h = __builtin_convertvector((f32x2{a, b}), bf16x2);
+  return __builtin_bit_cast(uint32_t, h);
 }
+__device__ __forceinline__ uint16_t f2bf(float f) { return (uint16_t)f2bf2(f, f); }
 
 __device__ __forceinline__ bf16x8 pack8(const uint16_t (&h)[8]) {
   union {
@@ -85,15 +92,18 @@ __device__ __forceinline__ bf16x8 lds8(const uint16_t* p) {  // 16-byte aligned
 
 // 8 FP32 values at p[0], p[stride], ... split into BF16 hi and lo terms.
 __device__ __forceinline__ void split8(const float* p, int stride, bf16x8& hi, bf16x8& lo) {
-  uint16_t h[8], l[8];
+  union {
+    uint32_t q[4];
+    bf16x8 v;
+  } h, l;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float v = p[e * stride];
-    h[e] = f2bf(v);
-    l[e] = f2bf(v - __uint_as_float((uint32_t)h[e] << 16));
+  for (int e = 0; e < 4; ++e) {
+    const float a = p[2 * e * stride], b = p[(2 * e + 1) * stride];
+    h.q[e] = f2bf2(a, b);
+    l.q[e] = f2bf2(a - __uint_as_float(h.q[e] << 16), b - __uint_as_float(h.q[e] & 0xFFFF0000u));
   }
-  hi = pack8(h);
-  lo = pack8(l);
+  hi = h.v;
+  lo = l.v;
 }
 
 __device__ __forceinline__ bf16x8 gather8(const uint16_t* p, int stride) {
@@ -115,68 +125,35 @@ __device__ __forceinline__ float sigm(float x) { return 1.f / (1.f + expf(-x)); 
 constexpr int kStageW2 = kHidAll * 64;
 __device__ void stage_weights(const float* __restrict__ w1, const float* __restrict__ w2,
                               uint16_t* s) {
-  for (int e = threadIdx.x; e < kHidAll * 64; e += (int)blockDim.x) {
-    const int r = e / 64, c = e % 64;
-    s[e] = c < kIn ? f2bf(w1[r * kIn + c]) : (uint16_t)0;
+  constexpr int kP1 = (kHidAll * kIn + kBwdThreads - 1) / kBwdThreads;
+  constexpr int kP2 = (kOut * kHid + kBwdThreads - 1) / kBwdThreads;
+  const int tid = threadIdx.x;
+  float v1[kP1], v2[kP2];  // every load issued before the first is used
+#pragma unroll
+  for (int q = 0; q < kP1; ++q) v1[q] = w1[min(tid + q * kBwdThreads, kHidAll * kIn - 1)];
+#pragma unroll
+  for (int q = 0; q < kP2; ++q) v2[q] = w2[min(tid + q * kBwdThreads, kOut * kHid - 1)];
+#pragma unroll
+  for (int q = 0; q < kP1; ++q) {
+    const int e = tid + q * kBwdThreads;
+    if (e < kHidAll * kIn) s[e / kIn * 64 + e % kIn] = f2bf(v1[q]);
   }
-  for (int e = threadIdx.x; e < 160 * kHid; e += (int)blockDim.x) {
-    const int pr = e / kHid, c = e % kHid;
-    const int hd = pr < 32 ? 0 : pr < 64 ? 1 : 2;
-    const int local = pr - head_base(hd);
-    s[kStageW2 + e] =
-        local < head_len(hd) ? f2bf(w2[(head_row(hd) + local) * kHid + c]) : (uint16_t)0;
+#pragma unroll
+  for (int q = 0; q < kP2; ++q) {
+    const int e = tid + q * kBwdThreads, r = e / kHid;
+    const int hd = r < head_row(1) ? 0 : r < head_row(2) ? 1 : 2;
+    if (e < kOut * kHid) s[kStageW2 + (head_base(hd) + r - head_row(hd)) * kHid + e % kHid] = f2bf(v2[q]);
   }
+  for (int e = tid; e < kHidAll * (64 - kIn); e += kBwdThreads)
+    s[e / (64 - kIn) * 64 + kIn + e % (64 - kIn)] = 0;
+  for (int e = tid; e < 50 * kHid; e += kBwdThreads)  // the padding rows
+    s[kStageW2 + pad_col(e / kHid) * kHid + e % kHid] = 0;
   __syncthreads();
-}
-
-// Forward weight operands of one lane (B operands, constant per launch).
-struct FwdW {
-  bf16x8 w1[6][2];  // layer 1: N-tile (hidden 16 nt ..), K-step (inputs 32 s ..)
-  bf16x8 w2[8];     // layer 2: op 1, colour 2, covariance 5 N-tiles
-};
-
-__device__ void load_fwd_weights(const uint16_t* s, FwdW& W) {
-  const int l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
-#pragma unroll
-  for (int nt = 0; nt < 6; ++nt)
-#pragma unroll
-    for (int k = 0; k < 2; ++k) W.w1[nt][k] = lds8(s + (16 * nt + m) * 64 + 32 * k + 8 * kq);
-  int t = 0;
-#pragma unroll
-  for (int hd = 0; hd < 3; ++hd)
-#pragma unroll
-    for (int nt = 0; nt < head_fwd_tiles(hd); ++nt)
-      W.w2[t++] = lds8(s + kStageW2 + (head_base(hd) + 16 * nt + m) * kHid + 8 * kq);
-}
-
-// Backward weight operands (B operands of dL/dh = W2^T dy and dL/dx = W1^T dz).
-struct BwdW {
-  bf16x8 w2t[10];   // [head K-step][N-tile]: op 1x2, colour 1x2, covariance 3x2
-  bf16x8 w1t[3][2]; // K-step (hidden 32 s ..), N-tile (inputs 16 nt ..)
-};
-
-__device__ void load_bwd_weights(const uint16_t* s, BwdW& W) {
-  const int l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
-  int t = 0;
-#pragma unroll
-  for (int hd = 0; hd < 3; ++hd)
-#pragma unroll
-    for (int k = 0; k < head_k_steps(hd); ++k)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-        W.w2t[t++] = gather8(s + kStageW2 + (head_base(hd) + 32 * k + 8 * kq) * kHid + 16 * nt + m,
-                             kHid);
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-      W.w1t[k][nt] = gather8(s + (32 * k + 8 * kq) * 64 + 16 * nt + m, 64);
 }
 
 // The backward runs 8 wavefronts per tile: wavefront w takes rows
 // 16 (w % 4) .. + 15 and half h = w / 4 of every product's N-tiles, so it
 // holds half of the weight operands.
-constexpr int kBwdThreads = 512;
 // layer-2 output tiles in order (head, N-tile): 0: (0,0), 1-2: (1,0..1),
 // 3-7: (2,0..4); half h computes tiles 4 h .. 4 h + 3
 __host__ __device__ constexpr int l2_head(int t) { return t == 0 ? 0 : t < 3 ? 1 : 2; }
@@ -245,149 +222,199 @@ __device__ void stage_bias(const DecIn& in, Bias& B) {
   __syncthreads();
 }
 
-// Forward of one tile of anchors a0 .. a0 + 63: sX (BF16 inputs), sH (BF16
-// hidden units), sY (FP32 y + b2 in padded columns). Ends with a barrier.
-// BATCH: the thread's feature loads all issued before the first is used
-// (faster in the backward, where the loop's loads wait one by one; slower in
-// the forward, measured).
-template <bool BATCH>
-__device__ void tile_forward(const DecIn& in, const Bias& B, int64_t a0, const FwdW& W,
-                             uint16_t* sX, uint16_t* sH, float* sY) {
-  const int tid = threadIdx.x;
-  const int64_t A = in.A;
-  if constexpr (BATCH) {
-    constexpr int kPer = kFeat * kTile / kThreads;  // 8
-    static_assert(kFeat * kTile % kThreads == 0, "whole rounds");
-    float fv[kPer];
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int e = tid + q * kThreads, k = e / kTile, m = e % kTile;
-      const int64_t ai = a0 + m;
-      fv[q] = in.feat[k * A + (ai < A ? ai : a0)];  // a0 < A: a valid row
-    }
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int e = tid + q * kThreads, k = e / kTile, m = e % kTile;
-      sX[m * kXS + k] = a0 + m < A ? f2bf(fv[q]) : (uint16_t)0;
-    }
-  } else {
-    for (int e = tid; e < kFeat * kTile; e += kThreads) {
-      const int k = e / kTile, m = e % kTile;
-      const int64_t ai = a0 + m;
-      sX[m * kXS + k] = ai < A ? f2bf(in.feat[k * A + ai]) : (uint16_t)0;
-    }
-  }
-  if (tid < kTile) {
-#pragma clang fp contract(off)
-    const int64_t ai = a0 + tid;
-    uint16_t d3[3] = {0, 0, 0};
-    if (ai < A) {
-      const double d0 = in.cx - (double)in.pos[ai];
-      const double d1 = in.cy - (double)in.pos[A + ai];
-      const double d2 = in.cz - (double)in.pos[2 * A + ai];
-      const double nrm = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-      d3[0] = f2bf((float)(d0 / nrm));
-      d3[1] = f2bf((float)(d1 / nrm));
-      d3[2] = f2bf((float)(d2 / nrm));
-    }
-    for (int j = 0; j < 3; ++j) sX[tid * kXS + kFeat + j] = d3[j];
-  }
-  __syncthreads();
-  const int l = tid & 63, w = tid >> 6, m = l & 15, kq = l >> 4;
-  const int row = 16 * w + m;
-  const bf16x8 xa0 = lds8(sX + row * kXS + 8 * kq);
-  const bf16x8 xa1 = lds8(sX + row * kXS + 32 + 8 * kq);
-#pragma unroll
-  for (int nt = 0; nt < 6; ++nt) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma(xa0, W.w1[nt][0], acc);
-    acc = mfma(xa1, W.w1[nt][1], acc);
-    const int hid = 16 * nt + m;
-    const float bb = B.b1[hid];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      sH[(16 * w + 4 * kq + i) * kHS + hid] = f2bf(fmaxf(acc[i] + bb, 0.f));
-  }
-  __syncthreads();
-  int t = 0;
-#pragma unroll
-  for (int hd = 0; hd < 3; ++hd) {
-    const bf16x8 ha = lds8(sH + row * kHS + kHid * hd + 8 * kq);
-#pragma unroll
-    for (int nt = 0; nt < head_fwd_tiles(hd); ++nt) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      acc = mfma(ha, W.w2[t++], acc);
-      const int local = 16 * nt + m;
-      const float bb = local < head_len(hd) ? B.b2[head_row(hd) + local] : 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sY[(16 * w + 4 * kq + i) * kYS + head_base(hd) + local] = acc[i] + bb;
-    }
-  }
-  __syncthreads();
+// The forward. A wavefront takes 16 anchors at a time and keeps them in
+// registers: products are formed transposed (weights as the A operand, anchors
+// as the columns of B and D), so lane (m, kq) loads the inputs 8 kq .. 8 kq + 7
+// of anchor m straight from memory, layer 1 leaves it hidden units 4 kq .. + 3
+// of each 16 in D, two lane swaps turn those into the 8 kq .. + 7 that layer 2
+// takes, and the rows of W2 are dealt out so that D rows 4 kq .. + 3 of an
+// output tile are one child's opacity and colour, scale or quaternion: what a
+// child needs is in one lane, and nothing waits for another wavefront.
+// Output tile t holds slots 4 t .. 4 t + 3 of four rows: slots 0 .. 9 opacity
+// and colour (two heads, hence two products) of child `slot`, 12 .. 21 its
+// scale (and mean), 22 .. 31 its quaternion.
+//
+// What bounds it: memory latency (two rounds of 16 wavefronts a compute unit
+// at 100k anchors), behind 84 MB to read and write. Against 64 anchors per
+// workgroup of four wavefronts that exchanged every layer through LDS, two
+// workgroups a compute unit: 49 -> 25 us at 100k anchors (3.3 TB/s), 17.4 ->
+// 9.5 us at 2k. Workgroups of 512, two a compute unit: the same.
+constexpr int kFwdThreads = 1024;
+constexpr int kFwdRows = 16;         // anchors per wavefront
+constexpr int kWS = 40;              // LDS row stride of the weights (elements)
+constexpr int kOutTiles = 8;
+
+// W2 row of row r (0 .. 15) of output tile t, -1: padding.
+__device__ __forceinline__ int out_row(int t, int r) {
+  const int slot = 4 * t + (r >> 2), i = r & 3;
+  if (slot < kKids) return i == 0 ? slot : head_row(1) + 3 * slot + i - 1;
+  if (slot < 12) return -1;
+  if (slot < 22) return i < 3 ? head_row(2) + 7 * (slot - 12) + i : -1;
+  return head_row(2) + 7 * (slot - 22) + 3 + i;
 }
 
-__global__ void __launch_bounds__(kThreads) k_decode_fwd(DecIn in, float* __restrict__ means,
-                                                         float* __restrict__ scales,
-                                                         float* __restrict__ quats,
-                                                         float* __restrict__ opac,
-                                                         float* __restrict__ rgb) {
-  __shared__ __align__(16) uint16_t sX[kTile * kXS];
-  __shared__ __align__(16) uint16_t sH[kTile * kHS];
-  __shared__ __align__(16) float sY[kTile * kYS];
-  __shared__ Bias sB;
-  FwdW W;
-  stage_bias(in, sB);
-  stage_weights(in.w1, in.w2, reinterpret_cast<uint16_t*>(sY));
-  load_fwd_weights(reinterpret_cast<const uint16_t*>(sY), W);
-  zero_x_pad(sX);
-  __syncthreads();
+__global__ void __launch_bounds__(kFwdThreads) k_decode_fwd(DecIn in, float* __restrict__ means,
+                                                            float* __restrict__ scales,
+                                                            float* __restrict__ quats,
+                                                            float* __restrict__ opac,
+                                                            float* __restrict__ rgb) {
+  __shared__ __align__(16) uint16_t sW1[kHidAll * kWS];    // inputs 35 .. 39 zero
+  __shared__ __align__(16) uint16_t sW2[(kOut + 1) * kWS];  // row kOut zero
+  __shared__ __align__(16) float sB1[kHidAll], sB2[kOutTiles * 16];
+  const int tid = threadIdx.x, l = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t A = in.A, N = A * kKids;
-  for (int64_t a0 = (int64_t)blockIdx.x * kTile; a0 < A; a0 += (int64_t)gridDim.x * kTile) {
-    tile_forward<false>(in, sB, a0, W, sX, sH, sY);
-    // the (child, anchor) items of a thread, unrolled: every anchor value is
-    // loaded before the first output is stored
-    constexpr int kRounds = (kKids * kTile + kThreads - 1) / kThreads;  // 3
-    float av[kRounds][12];  // child scale factors 3, pos 3, offsets 3, offset scaling 3
+  const int64_t step = (int64_t)gridDim.x * (kFwdThreads / kWave) * kFwdRows;
+  // wavefront w of every workgroup before wavefront w + 1 of any: few anchors
+  // still go to as many compute units as there are groups of 16
+  int64_t a0 = ((int64_t)w * gridDim.x + blockIdx.x) * kFwdRows;
+  float fv[8], pv[3];
+  const auto fetch = [&](int m, int kq) {  // anchor inputs (past the end: the last anchor's)
+    const int64_t ai = a0 + m < A ? a0 + m : A - 1;
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      const int it = threadIdx.x + r * kThreads;
-      const int j = it / kTile, m = it % kTile;
-      const int64_t ai = a0 + m;
-      if (it < kKids * kTile && ai < A) {
+    for (int e = 0; e < 8; ++e) fv[e] = in.feat[(8 * kq + e) * A + ai];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          av[r][d] = in.scaling[(3 + d) * A + ai];
-          av[r][3 + d] = in.pos[d * A + ai];
-          av[r][6 + d] = in.offsets[(3 * j + d) * A + ai];
-          av[r][9 + d] = in.scaling[d * A + ai];
-        }
+    for (int d = 0; d < 3; ++d) pv[d] = in.pos[d * A + ai];
+  };
+  fetch(l & 15, l >> 4);
+  {  // the weights, every load issued before the first is used
+    constexpr int kP1 = (kHidAll * kIn + kFwdThreads - 1) / kFwdThreads;
+    constexpr int kP2 = (kOut * kHid + kFwdThreads - 1) / kFwdThreads;
+    float v1[kP1], v2[kP2];
+#pragma unroll
+    for (int q = 0; q < kP1; ++q) v1[q] = in.w1[min(tid + q * kFwdThreads, kHidAll * kIn - 1)];
+#pragma unroll
+    for (int q = 0; q < kP2; ++q) v2[q] = in.w2[min(tid + q * kFwdThreads, kOut * kHid - 1)];
+    if (tid < kHidAll) sB1[tid] = in.b1[tid];
+    if (tid < kOutTiles * 16) {
+      const int r = out_row(tid >> 4, tid & 15);
+      sB2[tid] = r >= 0 ? in.b2[r] : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < kP1; ++q) {
+      const int e = tid + q * kFwdThreads;
+      if (e < kHidAll * kIn) sW1[e / kIn * kWS + e % kIn] = f2bf(v1[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < kP2; ++q) {
+      const int e = tid + q * kFwdThreads;
+      if (e < kOut * kHid) sW2[e / kHid * kWS + e % kHid] = f2bf(v2[q]);
+    }
+    for (int e = tid; e < kHidAll * (kWS - kIn); e += kFwdThreads)
+      sW1[e / (kWS - kIn) * kWS + kIn + e % (kWS - kIn)] = 0;
+    if (tid < kWS) sW2[kOut * kWS + tid] = 0;
+    __syncthreads();
+  }
+  const bf16x8 none = lds8(sW2 + kOut * kWS);  // zeros
+  for (; a0 < A; a0 += step) {
+    // the weights are read where they are used: the compiler must not see that
+    // they are the same in every turn, or it keeps them all in registers
+    int lane = l;
+    asm volatile("" : "+v"(lane));
+    const int m = lane & 15, kq = lane >> 4;
+    const int64_t ai = a0 + m < A ? a0 + m : A - 1;
+    const bool live = a0 + m < A;
+    // what the children need of the anchor (child 4 t + kq of output tile 3 + t)
+    float off[3][3], so[3], ss[3], pos[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      so[d] = in.scaling[d * A + ai];
+      ss[d] = in.scaling[(3 + d) * A + ai];
+      pos[d] = pv[d];
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        off[t][d] = in.offsets[(3 * min(4 * t + kq, kKids - 1) + d) * A + ai];
+    }
+    bf16x8 x0, x1 = none;
+    {
+      uint16_t h[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) h[e] = f2bf(fv[e]);
+      x0 = pack8(h);
+      if (kq == 0) {
+#pragma clang fp contract(off)
+        const double d0 = in.cx - (double)pv[0];
+        const double d1 = in.cy - (double)pv[1];
+        const double d2 = in.cz - (double)pv[2];
+        const double nrm = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+        const uint16_t g[8] = {f2bf((float)(d0 / nrm)), f2bf((float)(d1 / nrm)),
+                               f2bf((float)(d2 / nrm)), 0, 0, 0, 0, 0};
+        x1 = pack8(g);
       }
     }
+    // layer 1, and the hidden units as layer 2's operands
+    bf16x8 hid[3];
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      const int it = threadIdx.x + r * kThreads;
-      if (it >= kKids * kTile) break;
-      const int j = it / kTile, m = it % kTile;
-      const int64_t ai = a0 + m;
-      if (ai >= A) continue;
-      const float* y = sY + m * kYS;
-      const int64_t g = j * A + ai;
-      opac[g] = fmaxf(tanhf(y[j]), 0.f);
+    for (int hd = 0; hd < 3; ++hd) {
+      uint32_t p[2][2];  // [16 units][pair]: units 4 kq, + 1 and + 2, + 3
 #pragma unroll
-      for (int c = 0; c < 3; ++c) rgb[c * N + g] = sigm(y[32 + 3 * j + c]);
+      for (int u = 0; u < 2; ++u) {
+        const int nt = 2 * hd + u, row = 16 * nt + m;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc = mfma(lds8(sW1 + row * kWS + 8 * kq), x0, acc);
+        acc = mfma(lds8(kq == 0 ? sW1 + row * kWS + kFeat : sW2 + kOut * kWS), x1, acc);
+        const float4 bb = *reinterpret_cast<const float4*>(sB1 + 16 * nt + 4 * kq);
+        p[u][0] = f2bf2(fmaxf(acc[0] + bb.x, 0.f), fmaxf(acc[1] + bb.y, 0.f));
+        p[u][1] = f2bf2(fmaxf(acc[2] + bb.z, 0.f), fmaxf(acc[3] + bb.w, 0.f));
+      }
+      typedef unsigned u2 __attribute__((ext_vector_type(2)));
+      union {
+        uint32_t q[4];
+        bf16x8 v;
+      } o;
 #pragma unroll
-      for (int a = 0; a < 3; ++a) scales[a * N + g] = av[r][a] * sigm(y[64 + 7 * j + a]);
-      const float q0 = y[64 + 7 * j + 3], q1 = y[64 + 7 * j + 4], q2 = y[64 + 7 * j + 5],
-                  q3 = y[64 + 7 * j + 6];
-      const float inv = 1.f / sqrtf(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
-      quats[g] = q0 * inv;
-      quats[N + g] = q1 * inv;
-      quats[2 * N + g] = q2 * inv;
-      quats[3 * N + g] = q3 * inv;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) means[d * N + g] = av[r][3 + d] + av[r][6 + d] * av[r][9 + d];
+      for (int c = 0; c < 2; ++c) {
+        // rows of 16 lanes: (0 1 2 3), (0' 1' 2' 3') -> (0 1 0' 1'), (2 3 2' 3')
+        // -> (0 2 0' 2'), (1 3 1' 3')
+        const u2 a = __builtin_amdgcn_permlane32_swap(p[0][c], p[1][c], false, false);
+        const u2 b = __builtin_amdgcn_permlane16_swap(a.x, a.y, false, false);
+        o.q[c] = b.x;
+        o.q[2 + c] = b.y;
+      }
+      hid[hd] = o.v;
     }
-    __syncthreads();
+    a0 += step;
+    if (a0 < A) fetch(m, kq);  // the next anchors', behind the rest
+    a0 -= step;
+#pragma unroll
+    for (int t = 0; t < kOutTiles; ++t) {
+      const int r = out_row(t, m);
+      const uint16_t* wr = sW2 + (r >= 0 ? r : kOut) * kWS + 8 * kq;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      if (t < 3) {  // row 4 i of the tile: opacity (head 0); the others: colour (head 1)
+        const uint16_t* zr = sW2 + kOut * kWS;
+        acc = mfma(lds8((m & 3) == 0 ? wr : zr), hid[0], acc);
+        acc = mfma(lds8((m & 3) == 0 ? zr : wr), hid[1], acc);
+      } else {
+        acc = mfma(lds8(wr), hid[2], acc);
+      }
+      const float4 bb = *reinterpret_cast<const float4*>(sB2 + 16 * t + 4 * kq);
+      const float y0 = acc[0] + bb.x, y1 = acc[1] + bb.y, y2 = acc[2] + bb.z,
+                  y3 = acc[3] + bb.w;
+      const int slot = 4 * t + kq;
+      if (!live) continue;
+      if (slot < kKids) {
+        const int64_t g = slot * A + ai;
+        opac[g] = fmaxf(tanhf(y0), 0.f);
+        rgb[g] = sigm(y1);
+        rgb[N + g] = sigm(y2);
+        rgb[2 * N + g] = sigm(y3);
+      } else if (slot >= 12 && slot < 22) {
+        const int64_t g = (slot - 12) * A + ai;
+        scales[g] = ss[0] * sigm(y0);
+        scales[N + g] = ss[1] * sigm(y1);
+        scales[2 * N + g] = ss[2] * sigm(y2);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) means[d * N + g] = pos[d] + off[min(max(t - 3, 0), 2)][d] * so[d];
+      } else if (slot >= 22) {
+        const int64_t g = (slot - 22) * A + ai;
+        const float inv = 1.f / sqrtf(y0 * y0 + y1 * y1 + y2 * y2 + y3 * y3);
+        quats[g] = y0 * inv;
+        quats[N + g] = y1 * inv;
+        quats[2 * N + g] = y2 * inv;
+        quats[3 * N + g] = y3 * inv;
+      }
+    }
   }
 }
 
@@ -398,8 +425,9 @@ struct DecGrad {
   int accumulate;
 };
 
-// tile_forward for the backward's 8 wavefronts: the same sX, sH and sY,
-// with wavefront w computing rows 16 (w % 4) .. and the N-tiles of half
+// The forward of one tile of anchors a0 .. a0 + 63 for the backward's 8
+// wavefronts: sX (BF16 inputs), sH (BF16 hidden units), sY (FP32 y + b2 in
+// padded columns), wavefront w computing rows 16 (w % 4) .. and the N-tiles of half
 // h = w / 4 (hidden N-tiles 3 h .. 3 h + 2; output tiles 4 h .. 4 h + 3).
 // Ends with a barrier.
 __device__ void tile_forward_half(const DecIn& in, const Bias& B, int64_t a0, int h,
@@ -479,6 +507,7 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
   __shared__ __align__(16) float sY[kTile * kYS];   // y, then dL/dy in place
   __shared__ float sZ[kTile * kZS];   // dL/dz
   __shared__ float sD[kFeat * kDS];   // dL/dfeat, transposed for coalesced writes
+  __shared__ float sP[3][kKids][kTile];  // dL/dscale sigmoid(y)
   __shared__ Bias sB;
   const int tid = threadIdx.x, l = tid & 63, w = tid >> 6, m = l & 15, kq = l >> 4;
   const int wr = w & 3, h = w >> 2;  // row block and N-tile half of this wavefront
@@ -500,63 +529,14 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
   for (int q = 0; q < 3; ++q) accW1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
   float dbias = 0.f;  // threads 0..159: b2 padded column; 160..255: b1 unit
   for (int64_t a0 = (int64_t)blockIdx.x * kTile; a0 < A; a0 += (int64_t)gridDim.x * kTile) {
-    tile_forward_half(in, sB, a0, h, Wf, sX, sH, sY);
-    // offsets and scaling gradients, one thread per (anchor, axis d), the
-    // children in two groups of five whose values are loaded together
-    if (tid < 3 * kTile && a0 + tid % kTile < A) {
-      const int mm = tid % kTile, d = tid / kTile;
-      const int64_t ai = a0 + mm;
-      const float* y = sY + mm * kYS;
-      const float sc = in.scaling[d * A + ai];
-      float g_off = 0.f, g_sc = 0.f;
-      constexpr int kHalf = kKids / 2;
-#pragma unroll
-      for (int j0 = 0; j0 < kKids; j0 += kHalf) {
-        float dm[kHalf], off[kHalf], dsc[kHalf];
-#pragma unroll
-        for (int j = 0; j < kHalf; ++j) {
-          const int64_t g = (j0 + j) * A + ai;
-          dm[j] = gr.dmeans[d * N + g];
-          off[j] = in.offsets[(3 * (j0 + j) + d) * A + ai];
-          dsc[j] = gr.dscales[d * N + g];
-        }
-#pragma unroll
-        for (int j = 0; j < kHalf; ++j) {
-          g_off += dm[j] * off[j];
-          g_sc += dsc[j] * sigm(y[64 + 7 * (j0 + j) + d]);
-        }
-        if (gr.doffsets)
-#pragma unroll
-          for (int j = 0; j < kHalf; ++j)
-            put(gr.doffsets + (3 * (j0 + j) + d) * A + ai, dm[j] * sc, gr.accumulate);
-      }
-      if (gr.dscaling) {
-        put(gr.dscaling + d * A + ai, g_off, gr.accumulate);
-        put(gr.dscaling + (3 + d) * A + ai, g_sc, gr.accumulate);
-      }
-    }
-    __syncthreads();
-    // dL/dy in place of y; absent anchors and padded columns get zero (one
-    // (child, anchor) item per thread and round).
-    constexpr int kRounds = (kKids * kTile + kBwdThreads - 1) / kBwdThreads;  // 2
-#pragma unroll 1
-    for (int r = 0; r < kRounds; ++r) {
-      const int it = tid + r * kBwdThreads;
-      if (it >= kKids * kTile) break;
-      const int j = it / kTile, mm = it % kTile;
-      const int64_t ai = a0 + mm;
-      float* y = sY + mm * kYS;
-      float* yc = y + 32 + 3 * j;
-      float* yv = y + 64 + 7 * j;
-      if (ai >= A) {
-        y[j] = 0.f;
-        for (int c = 0; c < 3; ++c) yc[c] = 0.f;
-        for (int c = 0; c < 7; ++c) yv[c] = 0.f;
-        continue;
-      }
-      // the item's gradient loads, all issued before the first is used
-      float q[14];
-      const int64_t g = j * A + ai;
+    // What the elementwise part needs, read ahead of the tile's forward: the
+    // (child, anchor) items of round 0 (all threads) and round 1 (the first
+    // two wavefronts), and for the last three wavefronts, one axis d each, the
+    // offsets' part, which does not depend on the outputs.
+    float q0[14], q1[14], dm[kKids], off[kKids], sc = 0.f;
+    const auto read_item = [&](int it, float (&q)[14]) {
+      const int j = it / kTile;
+      const int64_t ai = a0 + it % kTile < A ? a0 + it % kTile : A - 1, g = j * A + ai;
       q[0] = gr.dopac[g];
 #pragma unroll
       for (int c = 0; c < 3; ++c) q[1 + c] = gr.drgb[c * N + g];
@@ -567,33 +547,83 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) q[10 + c] = gr.dquats[c * N + g];
+    };
+    static_assert(kKids * kTile - kBwdThreads == 2 * kWave, "round 1 is two wavefronts");
+    read_item(tid, q0);
+    if (w < 2) read_item(kBwdThreads + tid, q1);
+    const int d = w - 5;
+    if (d >= 0) {
+      const int64_t ai = a0 + l < A ? a0 + l : A - 1;
+      sc = in.scaling[d * A + ai];
+#pragma unroll
+      for (int j = 0; j < kKids; ++j) {
+        dm[j] = gr.dmeans[d * N + j * A + ai];
+        off[j] = in.offsets[(3 * j + d) * A + ai];
+      }
+    }
+    tile_forward_half(in, sB, a0, h, Wf, sX, sH, sY);
+    // dL/dy in place of y (one (child, anchor) item per thread and round; zero
+    // for absent anchors), and the items' dL/dscale sigmoid(y) for the scaling
+    // gradient
+    const auto item = [&](int it, const float (&q)[14]) {
+      const int j = it / kTile, mm = it % kTile;
+      const int64_t ai = a0 + mm;
+      float* y = sY + mm * kYS;
+      float* yc = y + 32 + 3 * j;
+      float* yv = y + 64 + 7 * j;
+      if (ai >= A) {
+        y[j] = 0.f;
+        for (int c = 0; c < 3; ++c) yc[c] = 0.f;
+        for (int c = 0; c < 7; ++c) yv[c] = 0.f;
+        return;
+      }
       const float th = tanhf(y[j]);
       y[j] = th > 0.f ? q[0] * (1.f - th * th) : 0.f;
+#pragma unroll
       for (int c = 0; c < 3; ++c) {
         const float s = sigm(yc[c]);
         yc[c] = q[1 + c] * s * (1.f - s);
       }
+#pragma unroll
       for (int a = 0; a < 3; ++a) {
         const float s = sigm(yv[a]);
+        sP[a][j][mm] = q[4 + a] * s;
         yv[a] = q[4 + a] * q[7 + a] * s * (1.f - s);
       }
-      const float q0 = yv[3], q1 = yv[4], q2 = yv[5], q3 = yv[6];
-      const float nrm = sqrtf(q0 * q0 + q1 * q1 + q2 * q2 + q3 * q3);
-      const float n0 = q0 / nrm, n1 = q1 / nrm, n2 = q2 / nrm, n3 = q3 / nrm;
+      const float r0 = yv[3], r1 = yv[4], r2 = yv[5], r3 = yv[6];
+      const float nrm = sqrtf(r0 * r0 + r1 * r1 + r2 * r2 + r3 * r3);
+      const float n0 = r0 / nrm, n1 = r1 / nrm, n2 = r2 / nrm, n3 = r3 / nrm;
       const float d0 = q[10], d1 = q[11], d2 = q[12], d3 = q[13];
       const float dot = n0 * d0 + n1 * d1 + n2 * d2 + n3 * d3;
       yv[3] = (d0 - n0 * dot) / nrm;
       yv[4] = (d1 - n1 * dot) / nrm;
       yv[5] = (d2 - n2 * dot) / nrm;
       yv[6] = (d3 - n3 * dot) / nrm;
+    };
+    item(tid, q0);
+    if (w < 2) item(kBwdThreads + tid, q1);
+    if (d >= 0 && a0 + l < A) {
+      const int64_t ai = a0 + l;
+      if (gr.doffsets)
+#pragma unroll
+        for (int j = 0; j < kKids; ++j)
+          put(gr.doffsets + (3 * j + d) * A + ai, dm[j] * sc, gr.accumulate);
+      float g_off = 0.f;
+#pragma unroll
+      for (int j = 0; j < kKids; ++j) g_off += dm[j] * off[j];
+      if (gr.dscaling) put(gr.dscaling + d * A + ai, g_off, gr.accumulate);
     }
-    // padded columns 10..31, 62..63, 134..159 (50 per row)
+    // padded columns
     for (int it = tid; it < kTile * 50; it += kBwdThreads) {
-      const int mm = it / 50, p = it % 50;
-      const int col = p < 22 ? 10 + p : p < 24 ? 62 + (p - 22) : 134 + (p - 24);
-      sY[mm * kYS + col] = 0.f;
+      sY[it / 50 * kYS + pad_col(it % 50)] = 0.f;
     }
     __syncthreads();
+    if (d >= 0 && gr.dscaling && a0 + l < A) {
+      float g_sc = 0.f;
+#pragma unroll
+      for (int j = 0; j < kKids; ++j) g_sc += sP[d][j][l];
+      put(gr.dscaling + (3 + d) * A + a0 + l, g_sc, gr.accumulate);
+    }
     const int row = 16 * wr + m;
     // dL/dh = W2^T dy per head (this wavefront's N-tile h of its 32 hidden
     // units), through the ReLU into dL/dz
@@ -786,10 +816,10 @@ extern "C" gs_status gs_anchor_decode_fwd(const gs_anchors* anchors, int64_t n_a
     return GS_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   const DecIn in = make_in(anchors, n_anchors, mlp, cd);
-  const int64_t tiles = (n_anchors + kTile - 1) / kTile;
-  const int nb = (int)(tiles < 512 ? tiles : 512);
+  const int64_t groups = (n_anchors + kFwdRows - 1) / kFwdRows;
+  const int nb = (int)(groups < 256 ? groups : 256);
   GS_TIMED("decode_fwd", st,
-           k_decode_fwd<<<nb, kThreads, 0, st>>>(in, out->means, out->log_scales, out->quats,
+           k_decode_fwd<<<nb, kFwdThreads, 0, st>>>(in, out->means, out->log_scales, out->quats,
                                                  out->opacity_logits, out->sh));
   GS_CHECK_LAUNCH();
   return GS_OK;
