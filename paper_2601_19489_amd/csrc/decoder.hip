@@ -46,12 +46,11 @@ __host__ __device__ constexpr int head_row(int h) {
   return h == 0 ? 0 : h == 1 ? 10 : h == 2 ? 40 : 110;
 }
 __host__ __device__ constexpr int head_len(int h) { return head_row(h + 1) - head_row(h); }
-__host__ __device__ constexpr int head_k_steps(int h) { return h == 2 ? 3 : 1; }
 // The 50 padding columns: 10 .. 31, 62, 63, 134 .. 159.
 __host__ __device__ constexpr int pad_col(int p) {
   return p < 22 ? 10 + p : p < 24 ? 62 + (p - 22) : 134 + (p - 24);
 }
-constexpr int kBwdThreads = 512;           // the backward's workgroup
+constexpr int kBwdThreads = 1024;          // the backward's workgroup
 // Per-workgroup partial sums in the workspace: dW1 [96][48], dW2 [160][32]
 // (padded rows), db1 [96], db2 [160].
 constexpr int kWsW1 = 0, kWsW2 = kWsW1 + kHidAll * 48, kWsB1 = kWsW2 + 160 * kHid,
@@ -151,49 +150,53 @@ __device__ void stage_weights(const float* __restrict__ w1, const float* __restr
   __syncthreads();
 }
 
-// The backward runs 8 wavefronts per tile: wavefront w takes rows
-// 16 (w % 4) .. + 15 and half h = w / 4 of every product's N-tiles, so it
-// holds half of the weight operands.
+// The backward runs 16 wavefronts per tile: wavefront w takes rows
+// 16 (w % 4) .. + 15 and quarter h = w / 4 of every product's N-tiles, so it
+// holds a quarter of the weight operands (three eighths where the tiles do not
+// divide by four).
+// layer 1: hidden N-tiles h and, for h < 2, 4 + h
 // layer-2 output tiles in order (head, N-tile): 0: (0,0), 1-2: (1,0..1),
-// 3-7: (2,0..4); half h computes tiles 4 h .. 4 h + 3
+// 3-7: (2,0..4); quarter h computes tiles 2 h and 2 h + 1
+// dL/dh: h = 0, 1: both N-tiles of head h; h = 2, 3: N-tile h - 2 of head 2
+// dL/dx: N-tile h for h < 2
 __host__ __device__ constexpr int l2_head(int t) { return t == 0 ? 0 : t < 3 ? 1 : 2; }
 __host__ __device__ constexpr int l2_ntile(int t) { return t == 0 ? 0 : t < 3 ? t - 1 : t - 3; }
 
-struct FwdWHalf {
-  bf16x8 w1[3][2];  // layer 1: hidden N-tiles 3 h .. 3 h + 2, both K-steps
-  bf16x8 w2[4];     // layer 2: output tiles 4 h .. 4 h + 3
+struct FwdWQuarter {
+  bf16x8 w1[2][2];  // [hidden N-tile][K-step]
+  bf16x8 w2[2];     // output tiles
 };
 
-__device__ void load_fwd_weights_half(const uint16_t* s, int h, FwdWHalf& W) {
+__device__ void load_fwd_weights(const uint16_t* s, int h, FwdWQuarter& W) {
   const int l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
 #pragma unroll
-  for (int j = 0; j < 3; ++j)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int k = 0; k < 2; ++k)
-      W.w1[j][k] = lds8(s + (16 * (3 * h + j) + m) * 64 + 32 * k + 8 * kq);
+      W.w1[j][k] = lds8(s + (16 * min(h + 4 * j, 5) + m) * 64 + 32 * k + 8 * kq);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int t = 4 * h + j;
+  for (int j = 0; j < 2; ++j) {
+    const int t = 2 * h + j;
     W.w2[j] = lds8(s + kStageW2 + (head_base(l2_head(t)) + 16 * l2_ntile(t) + m) * kHid + 8 * kq);
   }
 }
 
-struct BwdWHalf {
-  bf16x8 w2t[5];  // [head K-step], N-tile h: op 1, colour 1, covariance 3
-  bf16x8 w1t[3];  // K-step (hidden 32 s ..), N-tile h (inputs 16 h ..)
+struct BwdWQuarter {
+  // h < 2: W2^T, N-tiles 0, 1 of head h, then W1^T, K-steps 0 .. 2 (hidden
+  // 32 s ..) of N-tile h; else W2^T, K-steps 0 .. 2 of N-tile h - 2 of head 2
+  bf16x8 t[5];
 };
 
-__device__ void load_bwd_weights_half(const uint16_t* s, int h, BwdWHalf& W) {
+__device__ void load_bwd_weights(const uint16_t* s, int h, BwdWQuarter& W) {
   const int l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
-  int t = 0;
 #pragma unroll
-  for (int hd = 0; hd < 3; ++hd)
-#pragma unroll
-    for (int k = 0; k < head_k_steps(hd); ++k)
-      W.w2t[t++] = gather8(s + kStageW2 + (head_base(hd) + 32 * k + 8 * kq) * kHid + 16 * h + m,
-                           kHid);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) W.w1t[k] = gather8(s + (32 * k + 8 * kq) * 64 + 16 * h + m, 64);
+  for (int t = 0; t < 5; ++t) {
+    const int hd = h < 2 ? h : 2, k = h < 2 ? 0 : t, nt = h < 2 ? t : h - 2;
+    if (h < 2 ? t < 2 : t < 3)  // uniform
+      W.t[t] = gather8(s + kStageW2 + (head_base(hd) + 32 * k + 8 * kq) * kHid + 16 * nt + m, kHid);
+    else
+      W.t[t] = gather8(s + (32 * max(t - 2, 0) + 8 * kq) * 64 + 16 * (h & 1) + m, 64);
+  }
 }
 
 struct DecIn {
@@ -425,17 +428,14 @@ struct DecGrad {
   int accumulate;
 };
 
-// The forward of one tile of anchors a0 .. a0 + 63 for the backward's 8
+// The forward of one tile of anchors a0 .. a0 + 63 for the backward's 16
 // wavefronts: sX (BF16 inputs), sH (BF16 hidden units), sY (FP32 y + b2 in
-// padded columns), wavefront w computing rows 16 (w % 4) .. and the N-tiles of half
-// h = w / 4 (hidden N-tiles 3 h .. 3 h + 2; output tiles 4 h .. 4 h + 3).
-// Ends with a barrier.
-__device__ void tile_forward_half(const DecIn& in, const Bias& B, int64_t a0, int h,
-                                  const FwdWHalf& W, uint16_t* sX, uint16_t* sH, float* sY) {
-  const int tid = threadIdx.x;
+// padded columns), divided as above. Ends with a barrier.
+__device__ void tile_forward(const DecIn& in, const Bias& B, int64_t a0, int tid, int h,
+                             const FwdWQuarter& W, uint16_t* sX, uint16_t* sH, float* sY) {
   const int64_t A = in.A;
   {
-    constexpr int kPer = kFeat * kTile / kBwdThreads;  // 4
+    constexpr int kPer = kFeat * kTile / kBwdThreads;  // 2
     static_assert(kFeat * kTile % kBwdThreads == 0, "whole rounds");
     float fv[kPer];  // every load issued before the first is used
 #pragma unroll
@@ -471,11 +471,12 @@ __device__ void tile_forward_half(const DecIn& in, const Bias& B, int64_t a0, in
   const bf16x8 xa0 = lds8(sX + row * kXS + 8 * kq);
   const bf16x8 xa1 = lds8(sX + row * kXS + 32 + 8 * kq);
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
+  for (int j = 0; j < 2; ++j) {
+    if (h + 4 * j > 5) continue;  // uniform
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     acc = mfma(xa0, W.w1[j][0], acc);
     acc = mfma(xa1, W.w1[j][1], acc);
-    const int hid = 16 * (3 * h + j) + m;
+    const int hid = 16 * (h + 4 * j) + m;
     const float bb = B.b1[hid];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -483,8 +484,8 @@ __device__ void tile_forward_half(const DecIn& in, const Bias& B, int64_t a0, in
   }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int t = 4 * h + j, hd = l2_head(t), nt = l2_ntile(t);
+  for (int j = 0; j < 2; ++j) {
+    const int t = 2 * h + j, hd = l2_head(t), nt = l2_ntile(t);
     const bf16x8 ha = lds8(sH + row * kHS + kHid * hd + 8 * kq);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     acc = mfma(ha, W.w2[j], acc);
@@ -501,6 +502,14 @@ __device__ __forceinline__ void put(float* p, float v, int accumulate) {
   if (accumulate) *p += v; else *p = v;
 }
 
+// The backward. One workgroup a compute unit takes a tile of 64 anchors at a
+// time through the phases below; every weight-gradient sum adds the anchors of
+// its workgroup in order, so the grid and the tiles decide its bits.
+// What bounds it: a phase's LDS traffic and conversions, one after the other
+// between barriers (61% of the wavefronts' cycles are waits, a third of the
+// rest LDS). 99.6 -> 89 us at 100k anchors: BF16 conversions by instruction
+// instead of integer arithmetic 6 us, loads ahead of the tile's forward and 16
+// wavefronts instead of 8 the rest.
 __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr) {
   __shared__ __align__(16) uint16_t sX[kTile * kXS];
   __shared__ __align__(16) uint16_t sH[kTile * kHS];
@@ -509,32 +518,35 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
   __shared__ float sD[kFeat * kDS];   // dL/dfeat, transposed for coalesced writes
   __shared__ float sP[3][kKids][kTile];  // dL/dscale sigmoid(y)
   __shared__ Bias sB;
-  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6, m = l & 15, kq = l >> 4;
-  const int wr = w & 3, h = w >> 2;  // row block and N-tile half of this wavefront
-  FwdWHalf Wf;
-  BwdWHalf Wb;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w & 3, h = w >> 2;  // row block and N-tile quarter of this wavefront
+  FwdWQuarter Wf;
+  BwdWQuarter Wb;
   stage_bias(in, sB);
   stage_weights(in.w1, in.w2, reinterpret_cast<uint16_t*>(sY));
-  load_fwd_weights_half(reinterpret_cast<const uint16_t*>(sY), h, Wf);
-  load_bwd_weights_half(reinterpret_cast<const uint16_t*>(sY), h, Wb);
+  load_fwd_weights(reinterpret_cast<const uint16_t*>(sY), h, Wf);
+  load_bwd_weights(reinterpret_cast<const uint16_t*>(sY), h, Wb);
   zero_x_pad(sX);
   __syncthreads();
   const int64_t A = in.A, N = A * kKids;
-  // weight-gradient tiles of this wavefront: W2 (8 x 2 tiles) 2 w, 2 w + 1;
-  // W1 (6 x 3 tiles) w, w + 8, w + 16 (below 18)
-  f32x4 accW2[2], accW1[3];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) accW2[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int q = 0; q < 3; ++q) accW1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float dbias = 0.f;  // threads 0..159: b2 padded column; 160..255: b1 unit
+  // weight-gradient tiles of this wavefront: W2 (8 x 2 tiles) w; W1 (6 x 3
+  // tiles) w, and the last two for wavefronts 8 and 9 (which have no dL/dx)
+  f32x4 accW2 = {0.f, 0.f, 0.f, 0.f}, accW1[2] = {accW2, accW2};
+  const auto w1_tile = [&](int q) { return q == 0 ? w : w == 8 || w == 9 ? w + 8 : 18; };
+  float dbias = 0.f;  // bt 0..159: b2 padded column; 160..255: b1 unit
+  const int bt = (int)threadIdx.x - (kBwdThreads - 160 - kHidAll);
   for (int64_t a0 = (int64_t)blockIdx.x * kTile; a0 < A; a0 += (int64_t)gridDim.x * kTile) {
+    // the addresses below are formed anew in every turn: kept, they would take
+    // the registers of the reads ahead
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int l = tid & 63, m = l & 15, kq = l >> 4;
     // What the elementwise part needs, read ahead of the tile's forward: the
-    // (child, anchor) items of round 0 (all threads) and round 1 (the first
-    // two wavefronts), and for the last three wavefronts, one axis d each, the
-    // offsets' part, which does not depend on the outputs.
-    float q0[14], q1[14], dm[kKids], off[kKids], sc = 0.f;
-    const auto read_item = [&](int it, float (&q)[14]) {
+    // (child, anchor) items of the first ten wavefronts, and for three others,
+    // one axis d each, the offsets' part, which does not depend on the outputs
+    // (in the same registers).
+    float q[2 * kKids], sc = 0.f;
+    const auto read_item = [&](int it) {
       const int j = it / kTile;
       const int64_t ai = a0 + it % kTile < A ? a0 + it % kTile : A - 1, g = j * A + ai;
       q[0] = gr.dopac[g];
@@ -548,24 +560,24 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
 #pragma unroll
       for (int c = 0; c < 4; ++c) q[10 + c] = gr.dquats[c * N + g];
     };
-    static_assert(kKids * kTile - kBwdThreads == 2 * kWave, "round 1 is two wavefronts");
-    read_item(tid, q0);
-    if (w < 2) read_item(kBwdThreads + tid, q1);
-    const int d = w - 5;
-    if (d >= 0) {
+    static_assert(kTile == kWave && kKids + 3 <= kBwdThreads / kWave, "a wavefront per child");
+    if (w < kKids) read_item(tid);
+    const int d = w - kKids;
+    const bool axis = d >= 0 && d < 3;
+    if (axis) {
       const int64_t ai = a0 + l < A ? a0 + l : A - 1;
       sc = in.scaling[d * A + ai];
 #pragma unroll
       for (int j = 0; j < kKids; ++j) {
-        dm[j] = gr.dmeans[d * N + j * A + ai];
-        off[j] = in.offsets[(3 * j + d) * A + ai];
+        q[j] = gr.dmeans[d * N + j * A + ai];
+        q[kKids + j] = in.offsets[(3 * j + d) * A + ai];
       }
     }
-    tile_forward_half(in, sB, a0, h, Wf, sX, sH, sY);
-    // dL/dy in place of y (one (child, anchor) item per thread and round; zero
+    tile_forward(in, sB, a0, tid, h, Wf, sX, sH, sY);
+    // dL/dy in place of y (one (child, anchor) item per thread; zero
     // for absent anchors), and the items' dL/dscale sigmoid(y) for the scaling
     // gradient
-    const auto item = [&](int it, const float (&q)[14]) {
+    const auto item = [&](int it) {
       const int j = it / kTile, mm = it % kTile;
       const int64_t ai = a0 + mm;
       float* y = sY + mm * kYS;
@@ -600,17 +612,16 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
       yv[5] = (d2 - n2 * dot) / nrm;
       yv[6] = (d3 - n3 * dot) / nrm;
     };
-    item(tid, q0);
-    if (w < 2) item(kBwdThreads + tid, q1);
-    if (d >= 0 && a0 + l < A) {
+    if (w < kKids) item(tid);
+    if (axis && a0 + l < A) {
       const int64_t ai = a0 + l;
       if (gr.doffsets)
 #pragma unroll
         for (int j = 0; j < kKids; ++j)
-          put(gr.doffsets + (3 * j + d) * A + ai, dm[j] * sc, gr.accumulate);
+          put(gr.doffsets + (3 * j + d) * A + ai, q[j] * sc, gr.accumulate);
       float g_off = 0.f;
 #pragma unroll
-      for (int j = 0; j < kKids; ++j) g_off += dm[j] * off[j];
+      for (int j = 0; j < kKids; ++j) g_off += q[j] * q[kKids + j];
       if (gr.dscaling) put(gr.dscaling + d * A + ai, g_off, gr.accumulate);
     }
     // padded columns
@@ -618,70 +629,74 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
       sY[it / 50 * kYS + pad_col(it % 50)] = 0.f;
     }
     __syncthreads();
-    if (d >= 0 && gr.dscaling && a0 + l < A) {
+    if (axis && gr.dscaling && a0 + l < A) {
       float g_sc = 0.f;
 #pragma unroll
       for (int j = 0; j < kKids; ++j) g_sc += sP[d][j][l];
       put(gr.dscaling + (3 + d) * A + a0 + l, g_sc, gr.accumulate);
     }
     const int row = 16 * wr + m;
-    // dL/dh = W2^T dy per head (this wavefront's N-tile h of its 32 hidden
-    // units), through the ReLU into dL/dz
+    // dL/dh = W2^T dy per head, through the ReLU into dL/dz
     {
-      int t = 0;
-#pragma unroll
-      for (int hd = 0; hd < 3; ++hd) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < head_k_steps(hd); ++s) {
-          bf16x8 hi, lo;
-          split8(sY + row * kYS + head_base(hd) + 32 * s + 8 * kq, 1, hi, lo);
-          acc = mfma(hi, Wb.w2t[t], acc);
-          acc = mfma(lo, Wb.w2t[t], acc);
-          ++t;
-        }
-        const int hid = kHid * hd + 16 * h + m;
+      const auto to_z = [&](int hid, const f32x4& acc) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int r = 16 * wr + 4 * kq + i;
           sZ[r * kZS + hid] = sH[r * kHS + hid] != 0 ? acc[i] : 0.f;
         }
+      };
+      bf16x8 hi, lo;
+      if (h < 2) {
+        split8(sY + row * kYS + head_base(h) + 8 * kq, 1, hi, lo);
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+          acc = mfma(hi, Wb.t[nt], acc);
+          acc = mfma(lo, Wb.t[nt], acc);
+          to_z(kHid * h + 16 * nt + m, acc);
+        }
+      } else {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          split8(sY + row * kYS + head_base(2) + 32 * s + 8 * kq, 1, hi, lo);
+          acc = mfma(hi, Wb.t[s], acc);
+          acc = mfma(lo, Wb.t[s], acc);
+        }
+        to_z(kHid * 2 + 16 * (h - 2) + m, acc);
       }
     }
     __syncthreads();
     // dL/dfeat = (W1^T dz)[0..31], inputs 16 h .. 16 h + 15
-    {
+    if (h < 2) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < 3; ++s) {
         bf16x8 hi, lo;
         split8(sZ + row * kZS + 32 * s + 8 * kq, 1, hi, lo);
-        acc = mfma(hi, Wb.w1t[s], acc);
-        acc = mfma(lo, Wb.w1t[s], acc);
+        acc = mfma(hi, Wb.t[2 + s], acc);
+        acc = mfma(lo, Wb.t[2 + s], acc);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) sD[(16 * h + m) * kDS + 16 * wr + 4 * kq + i] = acc[i];
     }
     // weight gradients over this tile (K = anchors, two 32-anchor steps)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int idx = 2 * w + q, mt = idx >> 1, nt = idx & 1;
-      const int hd = mt == 0 ? 0 : mt < 3 ? 1 : 2;
-      const int lt = mt == 0 ? 0 : mt < 3 ? mt - 1 : mt - 3;
-      const int colb = head_base(hd) + 16 * lt;
+    {
+      const int mt = w >> 1, nt = w & 1, hd = l2_head(mt);
+      const int colb = head_base(hd) + 16 * l2_ntile(mt);
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const int k0 = 32 * s + 8 * kq;
         bf16x8 hi, lo;
         split8(sY + k0 * kYS + colb + m, kYS, hi, lo);
         const bf16x8 b = gather8(sH + k0 * kHS + kHid * hd + 16 * nt + m, kHS);
-        accW2[q] = mfma(hi, b, accW2[q]);
-        accW2[q] = mfma(lo, b, accW2[q]);
+        accW2 = mfma(hi, b, accW2);
+        accW2 = mfma(lo, b, accW2);
       }
     }
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int idx = w + 8 * q;
+    for (int q = 0; q < 2; ++q) {
+      const int idx = w1_tile(q);
       if (idx < 18) {
         const int mt = idx / 3, nt = idx % 3;
 #pragma unroll
@@ -695,10 +710,13 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
         }
       }
     }
-    if (tid < 160) {
-      for (int r = 0; r < kTile; ++r) dbias += sY[r * kYS + tid];
-    } else if (tid < 160 + kHidAll) {
-      for (int r = 0; r < kTile; ++r) dbias += sZ[r * kZS + tid - 160];
+    // the bias sums: by the last wavefronts, of which most have one tile less
+    if (bt >= 0 && bt < 160) {
+#pragma unroll 16
+      for (int r = 0; r < kTile; ++r) dbias += sY[r * kYS + bt];
+    } else if (bt >= 160) {
+#pragma unroll 16
+      for (int r = 0; r < kTile; ++r) dbias += sZ[r * kZS + bt - 160];
     }
     __syncthreads();
     if (gr.dfeat)
@@ -710,27 +728,24 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
     __syncthreads();
   }
   // partial sums of this workgroup
+  const int l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
   float* ws = gr.ws + (int64_t)blockIdx.x * kWsFloats;
+  {
+    const int mt = w >> 1, nt = w & 1, colb = head_base(l2_head(mt)) + 16 * l2_ntile(mt);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int idx = 2 * w + q, mt = idx >> 1, nt = idx & 1;
-    const int hd = mt == 0 ? 0 : mt < 3 ? 1 : 2;
-    const int lt = mt == 0 ? 0 : mt < 3 ? mt - 1 : mt - 3;
-    const int colb = head_base(hd) + 16 * lt;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ws[kWsW2 + (colb + 4 * kq + i) * kHid + 16 * nt + m] = accW2[q][i];
+    for (int i = 0; i < 4; ++i) ws[kWsW2 + (colb + 4 * kq + i) * kHid + 16 * nt + m] = accW2[i];
   }
 #pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    const int idx = w + 8 * q;
+  for (int q = 0; q < 2; ++q) {
+    const int idx = w1_tile(q);
     if (idx < 18) {
       const int mt = idx / 3, nt = idx % 3;
 #pragma unroll
       for (int i = 0; i < 4; ++i) ws[kWsW1 + (16 * mt + 4 * kq + i) * 48 + 16 * nt + m] = accW1[q][i];
     }
   }
-  if (tid < 160) ws[kWsB2 + tid] = dbias;
-  else if (tid < 160 + kHidAll) ws[kWsB1 + tid - 160] = dbias;
+  if (bt >= 0 && bt < 160) ws[kWsB2 + bt] = dbias;
+  else if (bt >= 160) ws[kWsB1 + bt - 160] = dbias;
 }
 
 // Sum of the per-workgroup partials (deterministic): a block takes 32
