@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(kEmitBlock) k_runs_emit(
     const float* __restrict__ splats, int64_t n, CamDev cam, const uint32_t* __restrict__ colh,
     int64_t cap, uint2* __restrict__ runs) {
   __shared__ SnugLds walk[kEmitBlock];
-  __shared__ uint32_t gid[kEmitBlock];
+  __shared__ uint32_t gid[kEmitBlock], mark[kEmitBlock];
   extern __shared__ uint32_t cw[];  // [kEmitWaves][tiles_x]
   const int tiles_x = cam.tiles_x;
   const int64_t nblk = gridDim.x, blk = blockIdx.x;
@@ -287,7 +287,7 @@ __global__ void __launch_bounds__(kEmitBlock) k_runs_emit(
     // the flattened list of the wavefront's (owner, column) entries
     SnugLds* lds = walk + w * kWave;
     const uint32_t incl = wave_incl_scan_u32(len);
-    const uint32_t total = __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1, kWave));
+    const uint32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
     lds[lane].s = s;
     lds[lane].tx0 = has ? (int)f : -1 - (int)f;  // negative: no rows (record rejected)
     lds[lane].excl = incl - len;
@@ -296,18 +296,13 @@ __global__ void __launch_bounds__(kEmitBlock) k_runs_emit(
     int nbits = 1;
     while ((1 << nbits) < tiles_x) ++nbits;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    uint32_t carry = 0;
     for (uint32_t c0 = 0; c0 < total; c0 += kWave) {
       const uint32_t c = c0 + (uint32_t)lane;
       const bool valid = c < total;
-      int o = 0;
+      const int o = round_owner(mark + w * kWave, c0, incl - len, len, carry);
       uint32_t tx = 0, word = 0;
       if (valid) {
-        int a = 0, b = kWave - 1;  // owner: last lane whose first entry is <= c
-        while (a < b) {
-          const int mid = (a + b + 1) >> 1;
-          if (lds[mid].excl <= c) a = mid; else b = mid - 1;
-        }
-        o = a;
         const int t0 = lds[o].tx0;
         const bool ohas = t0 >= 0;
         tx = (uint32_t)(ohas ? t0 : -1 - t0) + (c - lds[o].excl);
@@ -629,7 +624,7 @@ __global__ void __launch_bounds__(256) k_tile_count_variant(const float* __restr
                                                             uint32_t* __restrict__ counts) {
 #pragma clang fp contract(off)
   __shared__ SnugLds walk[256];
-  __shared__ uint32_t cnt[256];
+  __shared__ uint32_t cnt[256], mark[256];
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   Snug s;
   bool has = false;
@@ -643,8 +638,8 @@ __global__ void __launch_bounds__(256) k_tile_count_variant(const float* __restr
   if (variant == GS_TILES_COMPACT) {
     cnt[threadIdx.x] = 0;
     const int wbase = threadIdx.x & ~(kWave - 1);
-    wave_column_walk(has, s, cam.tile, cam.tiles_x, cam.tiles_y, walk + wbase,
-                     [&](int owner, int, int ty0, int ty1) {
+    wave_column_walk(has, s, cam.tile, cam.tiles_x, cam.tiles_y, walk + wbase, mark + wbase,
+                     [&](int owner, int, int ty0, int ty1, bool) {
                        if (ty1 >= ty0) atomicAdd(&cnt[wbase + owner], (uint32_t)(ty1 - ty0 + 1));
                      });
     if (i < n) counts[i] = cnt[threadIdx.x];

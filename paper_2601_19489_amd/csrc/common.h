@@ -218,53 +218,87 @@ __device__ __forceinline__ void snug_rows(const Snug& s, int tx, int tile, int t
 // on wave64): the 64 lanes of a wavefront walk the SnugBox columns of the 64
 // Gaussians they hold as one flattened list, 64 columns per round, so a
 // Gaussian spanning a hundred columns does not stall the other 63 lanes.
-// f(owner_lane, tx, ty0, ty1) runs once per column (ty0 > ty1: the column's
-// rows fall outside the grid). Every thread of the workgroup must call it
+// f(owner_lane, tx, ty0, ty1, first) runs once per column (ty0 > ty1: the
+// column's rows fall outside the grid), by all lanes together. Every thread of the workgroup must call it
 // (it synchronises the workgroup); `lds` is 64 entries of this wavefront's
-// scratch.
+// scratch, `mark` 64 words of it.
 struct SnugLds {
   Snug s;
   int tx0;
   uint32_t excl;
 };
 
-__device__ __forceinline__ uint32_t wave_incl_scan_u32_(uint32_t v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t o = __shfl_up(v, d, kWave);
-    if (lane >= d) v += o;
-  }
+// Inclusive scans over the wavefront in six data-parallel instructions (row
+// shifts, then the rows' last lanes carried on): through LDS shuffles each
+// step waited for the one before.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {  // 0 where no lane is read
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+  v += dpp_u32<0x111, 0xF>(v);
+  v += dpp_u32<0x112, 0xF>(v);
+  v += dpp_u32<0x114, 0xF>(v);
+  v += dpp_u32<0x118, 0xF>(v);
+  v += dpp_u32<0x142, 0xA>(v);
+  v += dpp_u32<0x143, 0xC>(v);
   return v;
+}
+__device__ __forceinline__ uint32_t wave_incl_max_u32(uint32_t v) {
+  v = max(v, dpp_u32<0x111, 0xF>(v));
+  v = max(v, dpp_u32<0x112, 0xF>(v));
+  v = max(v, dpp_u32<0x114, 0xF>(v));
+  v = max(v, dpp_u32<0x118, 0xF>(v));
+  v = max(v, dpp_u32<0x142, 0xA>(v));
+  v = max(v, dpp_u32<0x143, 0xC>(v));
+  return v;
+}
+
+// The owners of entries c0 .. c0 + 63 of a wavefront's flattened list, in which
+// lane l holds entries excl .. excl + len - 1: every owner that begins in the
+// round marks its first entry, and a running maximum carries it on to the
+// entries after it; `carry` (0 before the first round) is 1 + the owner of the
+// last entry of the round before. (A binary search over the 64 owners' first
+// entries is six LDS reads, each waiting for the last.) `mark`: 64 words of
+// this wavefront's LDS, whose operations complete in order.
+__device__ __forceinline__ int round_owner(uint32_t* mark, uint32_t c0, uint32_t excl,
+                                           uint32_t len, uint32_t& carry) {
+  const int lane = threadIdx.x & (kWave - 1);
+  mark[lane] = 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  if (len != 0 && excl - c0 < (uint32_t)kWave) mark[excl - c0] = (uint32_t)lane + 1u;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const uint32_t o = max(wave_incl_max_u32(mark[lane]), carry);
+  carry = __builtin_amdgcn_readlane(o, kWave - 1);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  return (int)o - 1;  // >= 0: entry 0 has an owner
 }
 
 template <typename F>
 __device__ __forceinline__ void wave_column_walk(bool valid, const Snug& s, int tile, int tiles_x,
-                                                 int tiles_y, SnugLds* lds, F&& f) {
+                                                 int tiles_y, SnugLds* lds, uint32_t* mark,
+                                                 F&& f) {
   const int lane = threadIdx.x & (kWave - 1);
   int tx0 = 0, tx1 = -1;
   if (valid) snug_columns(s, tile, tiles_x, tx0, tx1);
   const uint32_t ncols = (valid && tx1 >= tx0) ? (uint32_t)(tx1 - tx0 + 1) : 0u;
-  const uint32_t incl = wave_incl_scan_u32_(ncols);
-  const uint32_t total = __shfl(incl, kWave - 1, kWave);
+  const uint32_t incl = wave_incl_scan_u32(ncols);
+  const uint32_t total = __builtin_amdgcn_readlane(incl, kWave - 1);
   lds[lane].s = s;
   lds[lane].tx0 = tx0;
   lds[lane].excl = incl - ncols;
   __syncthreads();
+  uint32_t carry = 0;
   for (uint32_t c0 = 0; c0 < total; c0 += kWave) {
     const uint32_t c = c0 + (uint32_t)lane;
-    if (c < total) {
-      int lo = 0, hi = kWave - 1;  // owner: last lane whose first column is <= c
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (lds[mid].excl <= c) lo = mid; else hi = mid - 1;
-      }
-      const SnugLds& o = lds[lo];
-      const int tx = o.tx0 + (int)(c - o.excl);
-      int ty0, ty1;
-      snug_rows(o.s, tx, tile, tiles_y, ty0, ty1);
-      f(lo, tx, ty0, ty1);
-    }
+    const int lo = round_owner(mark, c0, incl - ncols, ncols, carry);
+    const SnugLds& o = lds[lo];
+    const int tx = o.tx0 + (int)(c - o.excl);
+    int ty0 = 1, ty1 = 0;
+    if (c < total) snug_rows(o.s, tx, tile, tiles_y, ty0, ty1);
+    // called by every lane: ty0 > ty1 where there is nothing; `first`: the
+    // owner's first entry of this round
+    f(lo, tx, ty0, ty1, c < total && (lane == 0 || c == o.excl));
   }
   __syncthreads();
 }
@@ -282,15 +316,6 @@ __device__ __forceinline__ void seq_column_walk(bool valid, const Snug& s, int t
     snug_rows(s, tx, tile, tiles_y, ty0, ty1);
     f(lane, tx, ty0, ty1);
   }
-}
-
-template <bool SEQ, typename F>
-__device__ __forceinline__ void column_walk(bool valid, const Snug& s, int tile, int tiles_x,
-                                            int tiles_y, SnugLds* lds, F&& f) {
-  if constexpr (SEQ)
-    seq_column_walk(valid, s, tile, tiles_x, tiles_y, f);
-  else
-    wave_column_walk(valid, s, tile, tiles_x, tiles_y, lds, f);
 }
 
 // ---------------------------------------------------------------------------

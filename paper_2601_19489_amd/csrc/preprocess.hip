@@ -119,7 +119,7 @@ __device__ __forceinline__ void preprocess_block(
     const float* __restrict__ sh, int64_t n, int deg, const CamDev& cam, int64_t blk,
     float* __restrict__ splats, uint32_t* __restrict__ depth_keys,
     uint32_t* __restrict__ tile_counts, SnugLds* walk, uint32_t* cnt, uint32_t* cfirst,
-    uint32_t* clast) {
+    uint32_t* clast, uint32_t* mark) {
   const int64_t i = blk * 256 + threadIdx.x;
   Snug s;
   bool has = false;
@@ -170,14 +170,38 @@ __device__ __forceinline__ void preprocess_block(
   cfirst[threadIdx.x] = 0xFFFFFFFFu;
   clast[threadIdx.x] = 0;
   const int wbase = threadIdx.x & ~(kWave - 1);
-  column_walk<SEQ>(has, s, cam.tile, cam.tiles_x, cam.tiles_y, walk + wbase,
-                   [&](int owner, int tx, int ty0, int ty1) {
-                     if (ty1 >= ty0) {
-                       atomicAdd(&cnt[wbase + owner], (uint32_t)(ty1 - ty0 + 1));
-                       atomicMin(&cfirst[wbase + owner], (uint32_t)tx);
-                       atomicMax(&clast[wbase + owner], (uint32_t)tx);
-                     }
-                   });
+  if constexpr (SEQ) {
+    seq_column_walk(has, s, cam.tile, cam.tiles_x, cam.tiles_y,
+                    [&](int owner, int tx, int ty0, int ty1) {
+                      if (ty1 >= ty0) {
+                        cnt[wbase + owner] += (uint32_t)(ty1 - ty0 + 1);
+                        cfirst[wbase + owner] = min(cfirst[wbase + owner], (uint32_t)tx);
+                        clast[wbase + owner] = (uint32_t)tx;
+                      }
+                    });
+  } else {
+    // A round's entries of one owner are neighbouring lanes with ascending
+    // columns, and the first of them adds up what they hold (three LDS atomics
+    // per entry instead, most on the same word, took a quarter of the kernel).
+    wave_column_walk(has, s, cam.tile, cam.tiles_x, cam.tiles_y, walk + wbase, mark + wbase,
+                     [&](int owner, int tx, int ty0, int ty1, bool first) {
+                       const int lane = threadIdx.x & (kWave - 1);
+                       const uint32_t len = ty1 >= ty0 ? (uint32_t)(ty1 - ty0 + 1) : 0u;
+                       const uint32_t incl = wave_incl_scan_u32(len);
+                       const uint64_t some = __ballot(len != 0), firsts = __ballot(first);
+                       const uint64_t above = firsts >> lane >> 1;  // the owners after this one
+                       const int end = above ? lane + __builtin_ctzll(above) : kWave - 1;
+                       const uint32_t upto = __shfl(incl, end, kWave);
+                       const uint64_t mine = some >> lane & (~0ull >> (kWave - 1 - (end - lane)));
+                       if (first && mine) {
+                         cnt[wbase + owner] += upto - (incl - len);
+                         cfirst[wbase + owner] =
+                             min(cfirst[wbase + owner], (uint32_t)(tx + __builtin_ctzll(mine)));
+                         clast[wbase + owner] =
+                             (uint32_t)(tx + kWave - 1 - __builtin_clzll(mine));
+                       }
+                     });
+  }
   if (i < n) {
     const uint32_t c = cnt[threadIdx.x];
     tile_counts[i] = c;
@@ -196,9 +220,9 @@ __global__ void __launch_bounds__(256) k_preprocess(
     const float* __restrict__ sh, int64_t n, CamDev cam, float* __restrict__ splats,
     uint32_t* __restrict__ depth_keys, uint32_t* __restrict__ tile_counts) {
   __shared__ SnugLds walk[256];
-  __shared__ uint32_t cnt[256], cfirst[256], clast[256];
+  __shared__ uint32_t cnt[256], cfirst[256], clast[256], mark[256];
   preprocess_block<SEQ>(means, log_scales, quats, logits, sh, n, DEG, cam, blockIdx.x, splats,
-                        depth_keys, tile_counts, walk, cnt, cfirst, clast);
+                        depth_keys, tile_counts, walk, cnt, cfirst, clast, mark);
 }
 
 // All views in one launch: blockIdx.y is the view.
@@ -215,11 +239,11 @@ __global__ void __launch_bounds__(256) k_preprocess_batched(
     const float* __restrict__ quats, const float* __restrict__ logits,
     const float* __restrict__ sh, int64_t n, PreBatch pb) {
   __shared__ SnugLds walk[256];
-  __shared__ uint32_t cnt[256], cfirst[256], clast[256];
+  __shared__ uint32_t cnt[256], cfirst[256], clast[256], mark[256];
   const int v = blockIdx.y;
   preprocess_block<SEQ>(means, log_scales, quats, logits, sh, n, DEG, pb.cam[v], blockIdx.x,
                         pb.splats[v], pb.depth_keys[v], pb.tile_counts[v], walk, cnt, cfirst,
-                        clast);
+                        clast, mark);
 }
 
 // ---------------------------------------------------------------------------

@@ -46,16 +46,6 @@ gs_status radix_pass(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t*
                      uint32_t* vals2_out = nullptr, int bits = 8, int vals2_stride = 1,
                      uint32_t* groups = nullptr);
 
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const uint32_t o = __shfl_up(v, d, kWave);
-    if (lane >= d) v += o;
-  }
-  return v;
-}
-
 // Exclusive scan over one workgroup of NTH threads (all threads call it):
 // returns the exclusive prefix of v; `total` receives the sum. wsum is LDS
 // scratch of NTH / 64 words; the call ends with a barrier.
