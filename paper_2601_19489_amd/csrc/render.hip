@@ -848,22 +848,33 @@ __device__ __forceinline__ int bwd_region_y(int r) {
 // the splat; tg is dL/dQ / (-o / 2), w the blend weight. The order of every
 // operation is written out, here and in the sums below, so that the gradients
 // do not depend on which of the walks forms them.
+// The first half does not need T and U: x = alpha, y = 1 / (1 - alpha), z = the
+// splat's colour (and depth) along dL/dC, w = G (-1: alpha is clamped).
+template <bool DEPTH>
+__device__ __forceinline__ float4 bwd_pixel_shape(float G, float o, float4 a2, float dC0,
+                                                  float dC1, float dC2, float dD) {
+#pragma clang fp contract(off)
+  const float oG = o * G;
+  const float al = fminf(kAlphaMax, oG);
+  float dcc = fmaf(dC2, a2.z, fmaf(dC0, a2.x, dC1 * a2.y));
+  if (DEPTH) dcc = fmaf(dD, a2.w, dcc);
+  return make_float4(al, __builtin_amdgcn_rcpf(1.f - al), dcc, oG <= kAlphaMax ? G : -1.f);
+}
+__device__ __forceinline__ void bwd_pixel_blend(float4 p, float& T, float& U, float& tg,
+                                                float& w) {
+#pragma clang fp contract(off)
+  const float Tb = T * p.y;  // transmittance in front of this splat
+  w = p.x * Tb;
+  const float dal = p.y * fmaf(T, p.z, -U);
+  tg = p.w >= 0.f ? dal * p.w : 0.f;  // no gradient through the clamp
+  U = fmaf(w, p.z, U);
+  T = Tb;
+}
 template <bool DEPTH>
 __device__ __forceinline__ void bwd_pixel(float G, float o, float4 a2, float dC0, float dC1,
                                           float dC2, float dD, float& T, float& U, float& tg,
                                           float& w) {
-#pragma clang fp contract(off)
-  const float oG = o * G;
-  const float al = fminf(kAlphaMax, oG);
-  const float rinv = __builtin_amdgcn_rcpf(1.f - al);
-  const float Tb = T * rinv;  // transmittance in front of this splat
-  w = al * Tb;
-  float dcc = fmaf(dC2, a2.z, fmaf(dC0, a2.x, dC1 * a2.y));
-  if (DEPTH) dcc = fmaf(dD, a2.w, dcc);
-  const float dal = rinv * fmaf(T, dcc, -U);
-  tg = oG <= kAlphaMax ? dal * G : 0.f;  // no gradient through the clamp
-  U = fmaf(w, dcc, U);
-  T = Tb;
+  bwd_pixel_blend(bwd_pixel_shape<DEPTH>(G, o, a2, dC0, dC1, dC2, dD), T, U, tg, w);
 }
 
 // The lane's sums over its PX pixels: m0, m1, m2 of tg and its ey, ey^2 moments,
@@ -942,7 +953,7 @@ __device__ __forceinline__ void bwd_reduce(float (&red)[GS_GRAD2D_COMPONENTS][N]
 // only T and U pass from one to the next. With the long regions of
 // bwd_region_coop, against one wavefront per tile walking the whole list:
 // 873 -> 335 us (300k Gaussians of about their spacing's size, 1600x1066),
-// 1476 -> 536 us (1M children of 100k anchors), 272 -> 90 us (1000 Gaussians,
+// 1476 -> 525 us (1M children of 100k anchors), 272 -> 73 us (1000 Gaussians,
 // 64x64), 583 -> 558 us (1M Gaussians of the surface scene, 1600x1066). With
 // 96 registers for five wavefronts a SIMD (a few spilled): 581 us for the last.
 template <int TILE, int PX, bool DEPTH>
@@ -1178,28 +1189,32 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
   }
 }
 
-// A region of four cells whose walk is long goes to a workgroup of four
-// wavefronts, one per cell: each walks the splats that reach its 16 x 4 pixels,
-// kCoopBatch list entries at a time, and leaves every lane's tg and w of each
-// in LDS; then the wavefronts share out the entries and form their sums from
-// the four cells' values, in the order in which one wavefront with four
-// pixels per lane forms them, so the gradients are the same to the bit. The
-// serial part of a walk is then a quarter of the pixels' terms instead of all
-// terms and sums. 1.6 times the work of one wavefront where every splat
-// reaches every cell, hence only for long walks.
-constexpr int kCoopBatch = 16;
+// A region of four cells whose walk is long goes to a workgroup of NW = 4 or 8
+// wavefronts, a cell of 16 x 4 pixels to each or to two of them, 16 list
+// entries at a time, in three steps. The shapes of a cell's splats depend on
+// nothing before them: with 8 wavefronts, two share a cell's entries. Then
+// one wavefront per cell walks T and U through them, six operations an entry.
+// Then the wavefronts share out the entries and form their sums from the four
+// cells' values, in the order in which one wavefront with four pixels per lane
+// forms them, so the gradients are the same to the bit. With 4 wavefronts a
+// cell's own walks T and U as it goes, and it is about 1.6 times the work of
+// one wavefront where every splat reaches every cell, hence only for long
+// walks.
+template <int NW>
 struct BwdCoopLds {
+  static constexpr int kWaves = NW, B = 16;  // list entries at a time
+  using Px = std::conditional_t<NW == 8, float4, float2>;
   float4 s0[kWave + 1], s1[kWave + 1], s2[kWave + 1];  // as in BwdLds, by list entry
   float t[kWave + 1];
   uint32_t sid[kWave + 1], cells[kWave + 1];
-  float2 tw[kCoopBatch][4][kWave];  // (tg, w) by entry, cell and lane
-  uint32_t hit[2][4];               // per cell: the batch's entries that some pixel blends
-  float red[GS_GRAD2D_COMPONENTS][kCoopBatch];
+  Px px[B][4][kWave];      // by entry, cell and lane: (tg, w), before that the shape
+  uint32_t hit[2][NW];     // by wavefront: the batch's entries that some pixel blends
+  float red[GS_GRAD2D_COMPONENTS][B];
   uint32_t most[4];
 };
 
-template <bool DEPTH>
-__device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, uint32_t start,
+template <int NW, bool DEPTH>
+__device__ __forceinline__ void bwd_region_coop(BwdCoopLds<NW>& L, int x0, int y0, uint32_t start,
                                                 const float* __restrict__ splats,
                                                 const uint32_t* __restrict__ vals, int W, int H,
                                                 float bg0, float bg1, float bg2,
@@ -1210,9 +1225,11 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
                                                 double* __restrict__ grad2d, int64_t n) {
 #pragma clang fp contract(fast)
   constexpr int NC = GS_GRAD2D_COMPONENTS, NCU = DEPTH ? NC : NC - 1;
-  constexpr int B = kCoopBatch, G = kBwdGroup;
+  constexpr int B = BwdCoopLds<NW>::B, G = kBwdGroup;
+  static_assert(NW == 4 || NW == 8, "one or two wavefronts to a cell");
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int cell = wv & 3;
   const size_t HW = (size_t)H * W;
   const int x = x0 + lane % 16;
   const float px = (float)x + 0.5f;
@@ -1232,7 +1249,7 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
       dC1[j] = dL_dimage[HW + p];
       dC2[j] = dL_dimage[2 * HW + p];
       if (DEPTH) dD[j] = dL_ddepth ? dL_ddepth[p] : 0.f;
-      if (j == wv) {
+      if (j == cell) {
         T = T_final[p];
         nc = n_contrib[p];
       }
@@ -1241,7 +1258,7 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
   float my_py = py[0], e0 = dC0[0], e1 = dC1[0], e2 = dC2[0], e3 = dD[0];
 #pragma unroll
   for (int j = 1; j < 4; ++j)
-    if (wv == j) {  // uniform
+    if (cell == j) {  // uniform
       my_py = py[j];
       e0 = dC0[j];
       e1 = dC1[j];
@@ -1252,7 +1269,7 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
   uint32_t most = nc;
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, kWave));
-  if (lane == 0) L.most[wv] = most;
+  if (lane == 0 && wv < 4) L.most[wv] = most;
   if (threadIdx.x == 0) {  // the filler: t < 0 skips it
     L.s0[kWave] = make_float4(0.f, 0.f, 1.f, 0.f);
     L.s1[kWave] = make_float4(1.f, -1.f, -1.f, 0.f);
@@ -1277,7 +1294,7 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
   int hi = (int)most, lo = max(hi - kWave, 0);
   if (wv == 0 && hi > 0) fetch(lo, hi);
   for (int turn = 0; hi > 0; ++turn) {
-    if (wv == (turn & 3)) {
+    if (wv == turn % NW) {
       uint32_t cells = 0;  // an id past n (never for a correct list) reaches nothing
       if ((int64_t)gid < n) {
         const float band = skip_band(rec[0].z, rec[0].w, rec[1].x, rec[1].y);
@@ -1292,12 +1309,13 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
       L.cells[lane] = cells;
     }
     const int nlo = max(lo - kWave, 0);
-    if (wv == ((turn + 1) & 3) && lo > 0) fetch(nlo, lo);
+    if (wv == (turn + 1) % NW && lo > 0) fetch(nlo, lo);
     __syncthreads();
-    const uint64_t mine = __ballot((L.cells[lane] >> wv) & 1u);
+    const uint64_t mine = __ballot((L.cells[lane] >> cell) & 1u);
     for (int b0 = (hi - lo - 1) / B * B, par = 0; b0 >= 0; b0 -= B, par ^= 1) {
-      // the cell's entries of this batch, last first, G at a time
+      // the shapes of the cell's entries of this batch, G at a time
       uint32_t todo = (uint32_t)(mine >> b0) & ((1u << B) - 1u), hit = 0;
+      if (NW == 8) todo &= wv < 4 ? 0x5555u : 0xAAAAu;
       while (todo != 0) {
         int k[G];
         float4 a0[G], a1[G], a2[G];
@@ -1332,29 +1350,59 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
           if (act[g] == 0) continue;  // uniform (the filler's t < 0 leaves it inactive)
           const float Gs = gauss(
               __builtin_amdgcn_inverse_ballot_w64(act[g]) ? Q[g] : __builtin_huge_valf());
-          float2 tw;
-          bwd_pixel<DEPTH>(Gs, a1[g].w, a2[g], e0, e1, e2, e3, T, U, tw.x, tw.y);
-          L.tw[k[g] - b0][wv][lane] = tw;
+          const float4 p = bwd_pixel_shape<DEPTH>(Gs, a1[g].w, a2[g], e0, e1, e2, e3);
+          if constexpr (NW == 8) {
+            L.px[k[g] - b0][cell][lane] = p;
+          } else {
+            float2 tw;
+            bwd_pixel_blend(p, T, U, tw.x, tw.y);
+            L.px[k[g] - b0][cell][lane] = tw;
+          }
           hit |= 1u << (k[g] - b0);
         }
       }
       if (lane == 0) L.hit[par][wv] = hit;
       __syncthreads();
-      // the sums: entry q by wavefront q % 4
-      const uint32_t h0 = L.hit[par][0], h1 = L.hit[par][1], h2 = L.hit[par][2],
-                     h3 = L.hit[par][3];
-      const uint32_t any = h0 | h1 | h2 | h3;
-      for (int q = wv; q < B; q += 4) {
-        if (!(__builtin_amdgcn_readfirstlane(any >> q) & 1u)) continue;  // uniform
-        const uint32_t of = __builtin_amdgcn_readfirstlane(
-            ((h0 >> q) & 1u) | ((h1 >> q) & 1u) << 1 | ((h2 >> q) & 1u) << 2 |
-            ((h3 >> q) & 1u) << 3);
+      uint32_t hits[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        hits[j] = __builtin_amdgcn_readfirstlane(L.hit[par][j] | (NW == 8 ? L.hit[par][NW - 4 + j] : 0u));
+      if (NW == 8 && wv < 4) {  // T and U through the cell's entries, last first
+        uint32_t left = wv == 0 ? hits[0] : wv == 1 ? hits[1] : wv == 2 ? hits[2] : hits[3];
+        constexpr int R = 4;  // entries read together
+        while (left != 0) {
+          int k[R];
+          float4 p[R];
+#pragma unroll
+          for (int g = 0; g < R; ++g) {
+            k[g] = left != 0 ? 31 - __builtin_clz(left) : -1;
+            if (left != 0) left &= ~(1u << k[g]);
+            if constexpr (NW == 8) p[g] = L.px[max(k[g], 0)][cell][lane];
+          }
+#pragma unroll
+          for (int g = 0; g < R; ++g) {
+            if (k[g] < 0) break;  // uniform
+            float tg, w;
+            bwd_pixel_blend(p[g], T, U, tg, w);
+            *reinterpret_cast<float2*>(&L.px[k[g]][cell][lane]) = make_float2(tg, w);
+          }
+        }
+      }
+      if (NW == 8) __syncthreads();
+      // the sums: entry q by wavefront q % NW
+      const uint32_t any = hits[0] | hits[1] | hits[2] | hits[3];
+#pragma unroll
+      for (int q = wv; q < B; q += NW) {
+        if (!((any >> q) & 1u)) continue;  // uniform
+        const uint32_t of = ((hits[0] >> q) & 1u) | ((hits[1] >> q) & 1u) << 1 |
+                            ((hits[2] >> q) & 1u) << 2 | ((hits[3] >> q) & 1u) << 3;
         const float4 a0 = L.s0[b0 + q], a1 = L.s1[b0 + q];
         float tg[4], w[4], ey[4], m0, m1, m2, c[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           // a cell without a blend adds zeros
-          const float2 tw = (of >> j) & 1u ? L.tw[q][j][lane] : make_float2(0.f, 0.f);
+          const float2 tw = (of >> j) & 1u ? *reinterpret_cast<const float2*>(&L.px[q][j][lane])
+                                           : make_float2(0.f, 0.f);
           tg[j] = tw.x;
           w[j] = tw.y;
           ey[j] = py[j] - a0.y;
@@ -1364,7 +1412,7 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds& L, int x0, int y0, u
         bwd_reduce<DEPTH>(L.red, q, lane, a0, a1.x, a1.w, ex, m0, m1, m2, c);
       }
       __syncthreads();
-      for (int e = threadIdx.x; e < B * NCU; e += 4 * kWave) {
+      for (int e = threadIdx.x; e < B * NCU; e += NW * kWave) {
         const int q = e / NCU, c = e - q * NCU;
         if (!((any >> q) & 1u)) continue;
         float a = L.red[c][q];
@@ -1400,15 +1448,22 @@ constexpr int kBwdSplit = 2048;  // regions, heaviest first, that may get a work
 // workgroups 0 .. split - 1 each look at one of the first regions and take it if
 // its tile's walk is long; the workgroups after them take the other regions,
 // one per wavefront.
-template <bool SPLIT>
+template <int NW, bool SPLIT>
 union BwdShared {
-  BwdLds one[4];
-  BwdCoopLds coop;
+  BwdLds one[NW];
+  BwdCoopLds<NW> coop;
 };
-template <>
-union BwdShared<false> {
-  BwdLds one[4];
+template <int NW>
+union BwdShared<NW, false> {
+  BwdLds one[NW];
 };
+// Launches of at most this many regions have 8 wavefronts to a workgroup, the
+// others (and the batched one) 4: where the walk of a workgroup decides, 8 are
+// faster, where the chip is full their third step costs more than it saves. 4
+// against 8: 90 and 73 us (16 regions), 153 and 122 us (144), 101 and 92 us
+// (950), 274 and 257 us (3600); 328 and 360 us, 527 and 746 us (6700 regions,
+// 300k Gaussians of about their spacing's size and 1M children of anchors).
+constexpr int64_t kBwdFewRegions = 4096;
 template <int TILE, int PX>
 constexpr bool bwd_can_split() { return PX == 4 && TILE >= 16; }
 template <int TILE, int PX>
@@ -1431,8 +1486,8 @@ __device__ __forceinline__ void bwd_one(Shared& L, int tile, int part,
                                         double* __restrict__ grad2d, int64_t n) {
   const int x0 = tile / tiles_y * TILE + bwd_region_x<TILE, PX>(part);
   const int y0 = tile % tiles_y * TILE + bwd_region_y<TILE, PX>(part);
-  if constexpr (std::is_same<Shared, BwdCoopLds>::value)
-    bwd_region_coop<DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1, bg2, T_final,
+  if constexpr (!std::is_same<Shared, BwdLds>::value)
+    bwd_region_coop<Shared::kWaves, DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1, bg2, T_final,
                            n_contrib, dL_dimage, dL_ddepth, grad2d, n);
   else
     bwd_region<TILE, PX, DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1, bg2,
@@ -1441,20 +1496,20 @@ __device__ __forceinline__ void bwd_one(Shared& L, int tile, int part,
 
 // order, work: the tiles heaviest first and each tile's largest n_contrib
 // (null: tile-id order, one wavefront per region).
-template <int TILE, int PX, bool DEPTH>
-__global__ void __launch_bounds__(4 * kWave) k_render_bwd(
+template <int TILE, int PX, bool DEPTH, int NW>
+__global__ void __launch_bounds__(NW* kWave) k_render_bwd(
     const float* __restrict__ splats, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ ranges, int W, int H, int nt, int tiles_y, float bg0, float bg1,
     float bg2, const float* __restrict__ T_final, const uint32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimage, const float* __restrict__ dL_ddepth,
     double* __restrict__ grad2d, int64_t n, const uint32_t* __restrict__ order,
     const uint32_t* __restrict__ work) {
-  __shared__ BwdShared<bwd_can_split<TILE, PX>()> L;
+  __shared__ BwdShared<NW, bwd_can_split<TILE, PX>()> L;
   constexpr int R = bwd_regions<TILE, PX>();
   const int split = bwd_split<TILE, PX>(nt, order != nullptr);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const bool first = (int)blockIdx.x < split;
-  const int item = first ? (int)blockIdx.x : ((int)blockIdx.x - split) * 4 + wv;
+  const int item = first ? (int)blockIdx.x : ((int)blockIdx.x - split) * NW + wv;
   if (item >= nt * R) return;
   const int rank = item / R;
   const int tile = order ? (int)order[rank] : rank;
@@ -1725,7 +1780,7 @@ template <int TILE, int PX, bool DEPTH>
 __global__ void __launch_bounds__(4 * kWave) k_render_bwd_batched(
     ViewSet vs, int64_t n, float bg0, float bg1, float bg2, uint32_t* queue,
     const uint32_t* __restrict__ order, const uint32_t* __restrict__ work) {
-  __shared__ BwdShared<bwd_can_split<TILE, PX>()> L;
+  __shared__ BwdShared<4, bwd_can_split<TILE, PX>()> L;
   __shared__ int s_item;
   constexpr int R = bwd_regions<TILE, PX>();
   const int total = vs.total * R, split = bwd_split<TILE, PX>(vs.total, order != nullptr);
@@ -1894,14 +1949,18 @@ static gs_status image_bwd(int64_t n, const CamDev& cd, const float* splats, con
     GS_CHECK_LAUNCH();
     order = tile_order;
   }
-#define GS_BWD2(TL, PXV, DEP)                                                                  \
-  k_render_bwd<TL, PXV, DEP><<<bwd_split<TL, PXV>(nt, order != nullptr) +                      \
-                                   div_up((int64_t)nt * bwd_regions<TL, PXV>(), 4),            \
-                               4 * kWave, 0, st>>>(                                            \
+#define GS_BWD3(TL, PXV, DEP, NW)                                                              \
+  k_render_bwd<TL, PXV, DEP, NW><<<bwd_split<TL, PXV>(nt, order != nullptr) +                  \
+                                       div_up((int64_t)nt * bwd_regions<TL, PXV>(), NW),       \
+                                   NW * kWave, 0, st>>>(                                       \
       splats, vals, ranges, cd.W, cd.H, nt, cd.tiles_y, bg[0], bg[1], bg[2], T_final,          \
       n_contrib, dL_dimage, dL_ddepth, grad2d, n, order, order ? tile_order + nt : nullptr)
+#define GS_BWD2(TL, PXV, DEP)                                                                  \
+  if (bwd_can_split<TL, PXV>() && order && nt * bwd_regions<TL, PXV>() <= kBwdFewRegions)      \
+    GS_BWD3(TL, PXV, DEP, (bwd_can_split<TL, PXV>() ? 8 : 4));                                 \
+  else GS_BWD3(TL, PXV, DEP, 4)
 #define GS_BWD(TL, PXV) \
-  if (dL_ddepth) GS_BWD2(TL, PXV, true); else GS_BWD2(TL, PXV, false)
+  if (dL_ddepth) { GS_BWD2(TL, PXV, true); } else { GS_BWD2(TL, PXV, false); }
   GS_TIMED("render_bwd", st, if (cd.tile == 8) { GS_BWD(8, 1); }
            else if (cd.tile == 16) {
              if (px == 4) { GS_BWD(16, 4); } else if (px == 2) { GS_BWD(16, 2); }
@@ -1911,6 +1970,7 @@ static gs_status image_bwd(int64_t n, const CamDev& cd, const float* splats, con
            });
 #undef GS_BWD
 #undef GS_BWD2
+#undef GS_BWD3
   GS_CHECK_LAUNCH();
   return GS_OK;
 }
@@ -2211,7 +2271,8 @@ extern "C" gs_status gs_render_bwd_batched(const gs_gaussians* g, int64_t n, int
   k_render_bwd_batched<TL, PXV, DEP><<<                                                 \
       persistent_grid(bwd_split<TL, PXV>(vs.total, order != nullptr) +                  \
                           vs.total * bwd_regions<TL, PXV>(),                            \
-                      div_up(tuning().persist_wgs * bwd_regions<TL, PXV>(), 4)),        \
+                      div_up(tuning().persist_wgs * bwd_regions<TL, PXV>(),             \
+                             4)),                                        \
       4 * kWave, 0, st>>>(vs, n, bg[0], bg[1], bg[2], queue, order,                         \
                       order ? tile_order + vs.total : nullptr)
 #define GS_BWDB(TL, PXV) \
