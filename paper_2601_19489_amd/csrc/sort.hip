@@ -216,9 +216,8 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_hist(const uint32_t* __r
 // tile's own workgroup of k_radix_scatter: the groups before its own, the
 // tiles before it in its group, and the lower digits' totals (at most 64 + 31
 // coalesced loads per thread). Against the histogram, a scan in two launches
-// and the scatter, per pass: 28.7 -> 22.9 us at
-// 1M keys (the scatter itself 14.2 -> 17.7), and two launches of 4.5 us fewer
-// for short arrays.
+// and the scatter, per pass: 28.7 -> 22.9 us at 1M keys (the scatter itself
+// 14.2 -> 17.7), and two launches of 4.5 us fewer for short arrays.
 constexpr int kRadixGroup = 32;
 __global__ void __launch_bounds__(kSortThreads) k_radix_count(const uint32_t* __restrict__ keys,
                                                               int64_t n, int shift,
