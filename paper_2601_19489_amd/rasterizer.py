@@ -149,8 +149,8 @@ class Rasterizer:
 
     def forward(self, p, check_overflow: bool = True):
         self.preprocess(p)
-        if not check_overflow:
-            self.bin_sort(check_overflow=False)
+        if not check_overflow or torch.cuda.is_current_stream_capturing():
+            self.bin_sort(check_overflow=check_overflow)  # a checked one refuses capture
             self.render_fwd()
             return self.image, self.depth
         # The pair count is read while the forward already runs (on an overflow
