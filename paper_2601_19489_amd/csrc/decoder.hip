@@ -38,6 +38,7 @@ constexpr int kOut = 110;                  // 10 + 30 + 70 outputs
 constexpr int kTile = 64;                  // anchors per workgroup iteration
 // LDS row strides (elements): BF16 inputs and hidden units, FP32 outputs
 constexpr int kXS = 72, kHS = 104, kYS = 161, kZS = 97, kDS = 65;
+constexpr int kTS = 72;  // transposed BF16 copies (a row per input or hidden unit)
 // Padded output columns: head h occupies columns 32 h .. 32 h + 31 (op,
 // colour) and 64 .. 159 (covariance); the forward computes 16, 32 and 80 of
 // them, the backward reads 32, 32 and 96.
@@ -89,6 +90,12 @@ __device__ __forceinline__ bf16x8 lds8(const uint16_t* p) {  // 16-byte aligned
   return u.v;
 }
 
+// Two FP32 values split into BF16 hi and lo terms.
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& lo) {
+  hi = f2bf2(a, b);
+  lo = f2bf2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
+}
+
 // 8 FP32 values at p[0], p[stride], ... split into BF16 hi and lo terms.
 __device__ __forceinline__ void split8(const float* p, int stride, bf16x8& hi, bf16x8& lo) {
   union {
@@ -96,11 +103,8 @@ __device__ __forceinline__ void split8(const float* p, int stride, bf16x8& hi, b
     bf16x8 v;
   } h, l;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float a = p[2 * e * stride], b = p[(2 * e + 1) * stride];
-    h.q[e] = f2bf2(a, b);
-    l.q[e] = f2bf2(a - __uint_as_float(h.q[e] << 16), b - __uint_as_float(h.q[e] & 0xFFFF0000u));
-  }
+  for (int e = 0; e < 4; ++e)
+    split2(p[2 * e * stride], p[(2 * e + 1) * stride], h.q[e], l.q[e]);
   hi = h.v;
   lo = l.v;
 }
@@ -432,7 +436,8 @@ struct DecGrad {
 // wavefronts: sX (BF16 inputs), sH (BF16 hidden units), sY (FP32 y + b2 in
 // padded columns), divided as above. Ends with a barrier.
 __device__ void tile_forward(const DecIn& in, const Bias& B, int64_t a0, int tid, int h,
-                             const FwdWQuarter& W, uint16_t* sX, uint16_t* sH, float* sY) {
+                             const FwdWQuarter& W, uint16_t* sX, uint16_t* sH, float* sY, uint16_t* sXT,
+                             uint16_t* sHT) {
   const int64_t A = in.A;
   {
     constexpr int kPer = kFeat * kTile / kBwdThreads;  // 2
@@ -447,7 +452,9 @@ __device__ void tile_forward(const DecIn& in, const Bias& B, int64_t a0, int tid
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const int e = tid + q * kBwdThreads, k = e / kTile, m = e % kTile;
-      sX[m * kXS + k] = a0 + m < A ? f2bf(fv[q]) : (uint16_t)0;
+      const uint16_t v = a0 + m < A ? f2bf(fv[q]) : (uint16_t)0;
+      sX[m * kXS + k] = v;
+      sXT[k * kTS + m] = v;
     }
   }
   if (tid < kTile) {
@@ -463,7 +470,10 @@ __device__ void tile_forward(const DecIn& in, const Bias& B, int64_t a0, int tid
       d3[1] = f2bf((float)(d1 / nrm));
       d3[2] = f2bf((float)(d2 / nrm));
     }
-    for (int j = 0; j < 3; ++j) sX[tid * kXS + kFeat + j] = d3[j];
+    for (int j = 0; j < 3; ++j) {
+      sX[tid * kXS + kFeat + j] = d3[j];
+      sXT[(kFeat + j) * kTS + tid] = d3[j];
+    }
   }
   __syncthreads();
   const int l = tid & 63, wr = (tid >> 6) & 3, m = l & 15, kq = l >> 4;
@@ -478,9 +488,14 @@ __device__ void tile_forward(const DecIn& in, const Bias& B, int64_t a0, int tid
     acc = mfma(xa1, W.w1[j][1], acc);
     const int hid = 16 * (h + 4 * j) + m;
     const float bb = B.b1[hid];
+    uint32_t v[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      v[i] = f2bf2(fmaxf(acc[2 * i] + bb, 0.f), fmaxf(acc[2 * i + 1] + bb, 0.f));
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      sH[(16 * wr + 4 * kq + i) * kHS + hid] = f2bf(fmaxf(acc[i] + bb, 0.f));
+      sH[(16 * wr + 4 * kq + i) * kHS + hid] = (uint16_t)(v[i / 2] >> (16 * (i & 1)));
+    *reinterpret_cast<uint2*>(sHT + hid * kTS + 16 * wr + 4 * kq) = make_uint2(v[0], v[1]);
   }
   __syncthreads();
 #pragma unroll
@@ -507,9 +522,11 @@ __device__ __forceinline__ void put(float* p, float v, int accumulate) {
 // its workgroup in order, so the grid and the tiles decide its bits.
 // What bounds it: a phase's LDS traffic and conversions, one after the other
 // between barriers (61% of the wavefronts' cycles are waits, a third of the
-// rest LDS). 99.6 -> 89 us at 100k anchors: BF16 conversions by instruction
+// rest LDS). 99.6 -> 85.5 us at 100k anchors: BF16 conversions by instruction
 // instead of integer arithmetic 6 us, loads ahead of the tile's forward and 16
-// wavefronts instead of 8 the rest.
+// wavefronts instead of 8 4 us, and the weight gradients' operands read 16
+// bytes at a time from transposed copies, instead of gathered (and dL/dz split
+// anew) by every tile that takes them, 5 us.
 __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr) {
   __shared__ __align__(16) uint16_t sX[kTile * kXS];
   __shared__ __align__(16) uint16_t sH[kTile * kHS];
@@ -517,6 +534,10 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
   __shared__ float sZ[kTile * kZS];   // dL/dz
   __shared__ float sD[kFeat * kDS];   // dL/dfeat, transposed for coalesced writes
   __shared__ float sP[3][kKids][kTile];  // dL/dscale sigmoid(y)
+  // What the weight gradients take along the anchors, 8 at a time: inputs,
+  // hidden units and dL/dz in its two terms, transposed as they are written
+  __shared__ __align__(16) uint16_t sXT[48 * kTS], sHT[kHidAll * kTS], sZh[kHidAll * kTS],
+      sZl[kHidAll * kTS];
   __shared__ Bias sB;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = w & 3, h = w >> 2;  // row block and N-tile quarter of this wavefront
@@ -527,6 +548,7 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
   load_fwd_weights(reinterpret_cast<const uint16_t*>(sY), h, Wf);
   load_bwd_weights(reinterpret_cast<const uint16_t*>(sY), h, Wb);
   zero_x_pad(sX);
+  for (int e = threadIdx.x; e < (48 - kIn) * kTS; e += kBwdThreads) sXT[kIn * kTS + e] = 0;
   __syncthreads();
   const int64_t A = in.A, N = A * kKids;
   // weight-gradient tiles of this wavefront: W2 (8 x 2 tiles) w; W1 (6 x 3
@@ -573,7 +595,7 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
         q[kKids + j] = in.offsets[(3 * j + d) * A + ai];
       }
     }
-    tile_forward(in, sB, a0, tid, h, Wf, sX, sH, sY);
+    tile_forward(in, sB, a0, tid, h, Wf, sX, sH, sY, sXT, sHT);
     // dL/dy in place of y (one (child, anchor) item per thread; zero
     // for absent anchors), and the items' dL/dscale sigmoid(y) for the scaling
     // gradient
@@ -639,11 +661,19 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
     // dL/dh = W2^T dy per head, through the ReLU into dL/dz
     {
       const auto to_z = [&](int hid, const f32x4& acc) {
+        float z[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int r = 16 * wr + 4 * kq + i;
-          sZ[r * kZS + hid] = sH[r * kHS + hid] != 0 ? acc[i] : 0.f;
+          z[i] = sH[r * kHS + hid] != 0 ? acc[i] : 0.f;
+          sZ[r * kZS + hid] = z[i];
         }
+        uint32_t zh[2], zl[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) split2(z[2 * i], z[2 * i + 1], zh[i], zl[i]);
+        const int at = hid * kTS + 16 * wr + 4 * kq;
+        *reinterpret_cast<uint2*>(sZh + at) = make_uint2(zh[0], zh[1]);
+        *reinterpret_cast<uint2*>(sZl + at) = make_uint2(zl[0], zl[1]);
       };
       bf16x8 hi, lo;
       if (h < 2) {
@@ -689,7 +719,7 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
         const int k0 = 32 * s + 8 * kq;
         bf16x8 hi, lo;
         split8(sY + k0 * kYS + colb + m, kYS, hi, lo);
-        const bf16x8 b = gather8(sH + k0 * kHS + kHid * hd + 16 * nt + m, kHS);
+        const bf16x8 b = lds8(sHT + (kHid * hd + 16 * nt + m) * kTS + k0);
         accW2 = mfma(hi, b, accW2);
         accW2 = mfma(lo, b, accW2);
       }
@@ -702,9 +732,9 @@ __global__ void __launch_bounds__(kBwdThreads) k_decode_bwd(DecIn in, DecGrad gr
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
           const int k0 = 32 * s + 8 * kq;
-          bf16x8 hi, lo;
-          split8(sZ + k0 * kZS + 16 * mt + m, kZS, hi, lo);
-          const bf16x8 b = gather8(sX + k0 * kXS + 16 * nt + m, kXS);
+          const bf16x8 hi = lds8(sZh + (16 * mt + m) * kTS + k0);
+          const bf16x8 lo = lds8(sZl + (16 * mt + m) * kTS + k0);
+          const bf16x8 b = lds8(sXT + (16 * nt + m) * kTS + k0);
           accW1[q] = mfma(hi, b, accW1[q]);
           accW1[q] = mfma(lo, b, accW1[q]);
         }
