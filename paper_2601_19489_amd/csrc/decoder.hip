@@ -272,9 +272,12 @@ __global__ void __launch_bounds__(kFwdThreads) k_decode_fwd(DecIn in, float* __r
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t A = in.A, N = A * kKids;
   const int64_t step = (int64_t)gridDim.x * (kFwdThreads / kWave) * kFwdRows;
-  // wavefront w of every workgroup before wavefront w + 1 of any: few anchors
-  // still go to as many compute units as there are groups of 16
-  int64_t a0 = ((int64_t)w * gridDim.x + blockIdx.x) * kFwdRows;
+  // two neighbouring groups of 16 (a 128-byte line of every array) to a
+  // workgroup, whose chiplet then reads the line once (groups dealt singly:
+  // 57 instead of 28 MB read at 100k anchors); wavefronts 2 w, 2 w + 1 of every
+  // workgroup before 2 w + 2 of any, so few anchors still go to many compute
+  // units
+  int64_t a0 = (((int64_t)(w >> 1) * gridDim.x + blockIdx.x) * 2 + (w & 1)) * kFwdRows;
   float fv[8], pv[3];
   const auto fetch = [&](int m, int kq) {  // anchor inputs (past the end: the last anchor's)
     const int64_t ai = a0 + m < A ? a0 + m : A - 1;
@@ -862,7 +865,7 @@ extern "C" gs_status gs_anchor_decode_fwd(const gs_anchors* anchors, int64_t n_a
   hipStream_t st = (hipStream_t)stream;
   const DecIn in = make_in(anchors, n_anchors, mlp, cd);
   const int64_t groups = (n_anchors + kFwdRows - 1) / kFwdRows;
-  const int nb = (int)(groups < 256 ? groups : 256);
+  const int nb = (int)(groups < 512 ? (groups + 1) / 2 : 256);
   GS_TIMED("decode_fwd", st,
            k_decode_fwd<<<nb, kFwdThreads, 0, st>>>(in, out->means, out->log_scales, out->quats,
                                                  out->opacity_logits, out->sh));
