@@ -244,7 +244,7 @@ __device__ void stage_bias(const DecIn& in, Bias& B) {
 // What bounds it: memory latency (two rounds of 16 wavefronts a compute unit
 // at 100k anchors), behind 84 MB to read and write. Against 64 anchors per
 // workgroup of four wavefronts that exchanged every layer through LDS, two
-// workgroups a compute unit: 49 -> 25 us at 100k anchors (3.3 TB/s), 17.4 ->
+// workgroups a compute unit: 49 -> 23 us at 100k anchors (3.6 TB/s), 17.4 ->
 // 9.5 us at 2k. Workgroups of 512, two a compute unit: the same.
 constexpr int kFwdThreads = 1024;
 constexpr int kFwdRows = 16;         // anchors per wavefront
