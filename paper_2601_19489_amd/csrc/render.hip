@@ -121,6 +121,18 @@ __device__ __forceinline__ uint32_t cells_reached(float x0, float y0, float4 r0,
   return m;
 }
 
+// A splat whose colour, depth or opacity is not finite (or so large that their
+// sum is not) has to leave the pixels that do not blend it as they are, which a
+// weight of 0 does not. A wavefront whose batch of the list holds such a splat
+// walks that batch splat by splat, under the mask of the pixels that blend it.
+// (The mask in the ordinary walk costs the forward 2 to 15%, a branch around
+// the odd splats of a group 1 to 12%, a walk of its own nothing.)
+constexpr uint32_t kOddSplat = 1u << 31;  // among the cells' bits
+__device__ __forceinline__ bool odd_splat(float4 r1, float4 r2) {  // (c, t, o, z), (r, g, b, -)
+  return !(fabsf(r2.x) + fabsf(r2.y) + fabsf(r2.z) + fabsf(r1.w) + fabsf(r1.z) <
+           __builtin_huge_valf());
+}
+
 // 2 x + (the lane's bit of m), one instruction.
 __device__ __forceinline__ uint32_t shift_in(uint32_t x, uint64_t m) {
   uint32_t r;
@@ -152,7 +164,7 @@ struct FwdCells {
 
 // Stage the record of Gaussian g (g >= n: a splat that blends nowhere, since
 // its t < 0 skips it) as entry q, with the cells of the TILE x TILE tile at
-// (x0, y0) that it reaches.
+// (x0, y0) that it reaches (and kOddSplat).
 template <int TILE, class Lds>
 __device__ __forceinline__ void fwd_stage(Lds& L, int q, const float* __restrict__ splats,
                                           uint32_t g, int64_t n, float x0, float y0) {
@@ -170,7 +182,7 @@ __device__ __forceinline__ void fwd_stage(Lds& L, int q, const float* __restrict
                                                   FwdCells::y);
   }
   L.t[q] = r1.y;
-  L.cells[q] = cells;
+  L.cells[q] = (int64_t)g < n && odd_splat(r1, r2) ? cells | kOddSplat : cells;
   L.s0[q] = make_float4(r0.x, r0.y, r0.z, r0.w + r0.w);  // exact
   L.s1[q] = make_float4(r1.x, r1.y - band, r1.y + band, r1.z);
   L.s2[q] = make_float4(r2.x, r2.y, r2.z, r1.w);
@@ -411,12 +423,14 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB, TILE * TILE / PX>& L, int t
     // the wavefront's list: the splats that reach its cells, in order (with
     // CKPT every splat, since a checkpoint is due at fixed positions)
     int m = 0;
+    uint64_t odd = 0;
     for (int base = 0; base < cnt; base += kWave) {
       constexpr uint32_t kMine = (1u << PX) - 1u;
       const int q = base + lane;
-      const bool reach =
-          q < cnt && (CKPT || ((L.cells[min(q, NB)] >> (wv * PX)) & kMine) != 0u);
+      const uint32_t cells = L.cells[min(q, NB)];
+      const bool reach = q < cnt && (CKPT || ((cells >> (wv * PX)) & kMine) != 0u);
       const uint64_t bal = __ballot(reach);
+      odd |= __ballot(reach && (cells & kOddSplat) != 0u);
       if (reach)
         list[m + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
                                            __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))] =
@@ -426,6 +440,58 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB, TILE * TILE / PX>& L, int t
     if (lane < G) list[m + lane] = 16u * NB;
     __builtin_amdgcn_wave_barrier();  // a wavefront's LDS operations complete in order
     const uint32_t rel = b - start;
+    // the checkpoint due before the splat at list position pos, if any
+    const auto checkpoint = [&](uint32_t pos) {
+      if (!CKPT || pos % kCkptInterval != 0) return;
+      const uint32_t bk = pos / kCkptInterval;
+#pragma unroll
+      for (int j = 0; j < PX; ++j) {
+        if (__builtin_amdgcn_inverse_ballot_w64(done[j]) || bk >= (uint32_t)nbk) continue;
+        constexpr int NP = TILE * TILE;
+        const int pi = (FwdCells::y(wv * PX + j) + lane / 8) * TILE + FwdCells::x(wv * PX + j) +
+                       lane % 8;
+        float* c = ckpt + ((size_t)tile * nbk + bk) * kCkptVals * NP + pi;
+        c[0] = T[j];
+        c[NP] = C0[j];
+        c[2 * NP] = C1[j];
+        c[3 * NP] = C2[j];
+        c[4 * NP] = D[j];
+      }
+    };
+    if (odd != 0) {  // splat by splat, the same operations in the same order
+#pragma unroll 1
+      for (int i = 0; i < m && !alldone; ++i) {
+        const int q = (int)(list[i] / 16u);
+        const uint32_t pos = rel + (uint32_t)q;
+        const float4 a0 = L.s0[q], a1 = L.s1[q], a2 = L.s2[q];
+        checkpoint(pos);
+        alldone = true;
+#pragma unroll
+        for (int j = 0; j < PX; ++j) {
+          const float Q = eval_q(px[j], py[j], a0.x, a0.y, a0.z, a0.w, a1.x).Q;
+          uint64_t skip = __ballot(Q > a1.z);
+          if (~(skip | __ballot(Q <= a1.y)) != 0)
+            skip = __ballot(skips_f64(L.t[q], px[j], py[j], a0.x, a0.y, a0.z, 0.5f * a0.w, a1.x));
+          const float al = fminf(kAlphaMax, a1.w * gauss(Q));
+          const float Tn = T[j] * (1.f - al);
+          const uint64_t low = __ballot(Tn < kTStop);
+          const uint64_t none = skip | done[j] | low;  // no blend
+          done[j] |= low & ~skip;
+          if (!__builtin_amdgcn_inverse_ballot_w64(none)) {
+            const float w = al * T[j];
+            C0[j] = fmaf(a2.x, w, C0[j]);
+            C1[j] = fmaf(a2.y, w, C1[j]);
+            C2[j] = fmaf(a2.z, w, C2[j]);
+            D[j] = fmaf(a2.w, w, D[j]);
+            T[j] = Tn;
+            last[j] = pos + 1u;
+            if (CKPT && pos >= (uint32_t)nbk * kCkptInterval) atomicOr(ovf, 1u);
+          }
+          alldone = alldone && done[j] == ~0ull;
+        }
+      }
+      continue;
+    }
     for (int i0 = 0; i0 < m && !alldone; i0 += 32) {
       const int i1 = min(i0 + 32, m);
       uint32_t hist[PX];  // per splat walked, newest in bit 0: not blended
@@ -479,25 +545,7 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB, TILE * TILE / PX>& L, int t
           for (int j = 0; j < PX; ++j) al[g][j] = fminf(kAlphaMax, a1[g].w * gauss(Q[g][j]));
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-          if (CKPT) {
-            const uint32_t pos = rel + off[g] / 16u;
-            if (off[g] < 16u * NB && (pos % kCkptInterval) == 0) {
-              const uint32_t bk = pos / kCkptInterval;
-#pragma unroll
-              for (int j = 0; j < PX; ++j) {
-                if (__builtin_amdgcn_inverse_ballot_w64(done[j]) || bk >= (uint32_t)nbk) continue;
-                constexpr int NP = TILE * TILE;
-                const int pi = (FwdCells::y(wv * PX + j) + lane / 8) * TILE +
-                               FwdCells::x(wv * PX + j) + lane % 8;
-                float* c = ckpt + ((size_t)tile * nbk + bk) * kCkptVals * NP + pi;
-                c[0] = T[j];
-                c[NP] = C0[j];
-                c[2 * NP] = C1[j];
-                c[3 * NP] = C2[j];
-                c[4 * NP] = D[j];
-              }
-            }
-          }
+          if (CKPT && off[g] < 16u * NB) checkpoint(rel + off[g] / 16u);
           // the step in select form: every pixel runs it, and a skipped,
           // stopped or finished pixel changes nothing (no divergent branches)
           alldone = true;
@@ -509,6 +557,7 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB, TILE * TILE / PX>& L, int t
             done[j] |= low & ~skip[g][j];
             const bool nb = __builtin_amdgcn_inverse_ballot_w64(none);
             // weight 0 when not blending: adding c * 0 leaves the sums unchanged
+            // (c is finite: no odd splat here)
             const float w = nb ? 0.f : al[g][j] * T[j];
             C0[j] = fmaf(a2[g].x, w, C0[j]);
             C1[j] = fmaf(a2[g].y, w, C1[j]);
@@ -552,8 +601,12 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB, TILE * TILE / PX>& L, int t
 // tiles: 299 against 300 us on the 1920x1080 view of the surface scene, 138
 // against 145 us at 300k Gaussians of about their spacing's size. 32-pixel
 // tiles have 16 wavefronts to a workgroup: two of them need 8 (372 against 455
-// us with one). With several pixels per lane the registers decide.
-constexpr int fwd_waves(int tile, int px) { return px > 1 ? 1 : tile == 32 ? 8 : 7; }
+// us with one). With two pixels per lane the registers decide; with four, 128
+// registers (142 with the walk of odd splats, at 32-pixel tiles: 355 against
+// 339 us on the surface scene).
+constexpr int fwd_waves(int tile, int px) {
+  return px == 4 ? 4 : px == 2 ? 1 : tile == 32 ? 8 : 7;
+}
 
 template <int TILE, int PX>
 __global__ void __launch_bounds__(TILE* TILE / PX)
@@ -866,7 +919,7 @@ __device__ __forceinline__ void bwd_pixel_blend(float4 p, float& T, float& U, fl
   const float Tb = T * p.y;  // transmittance in front of this splat
   w = p.x * Tb;
   const float dal = p.y * fmaf(T, p.z, -U);
-  tg = p.w >= 0.f ? dal * p.w : 0.f;  // no gradient through the clamp
+  tg = p.w > 0.f ? dal * p.w : 0.f;  // none through the clamp or with G = 0 (U may be NaN)
   U = fmaf(w, p.z, U);
   T = Tb;
 }
@@ -1035,6 +1088,7 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
                                         [](int) { return 0; }, [](int i) { return CH * i; });
     }
     const uint64_t reach = __ballot(cells != 0);
+    const bool odd = __ballot(cells != 0 && odd_splat(rec[1], rec[2])) != 0;
     const int m = (int)__popcll(reach);
     if (cells != 0) {
       const int k = (int)__builtin_amdgcn_mbcnt_hi(
@@ -1054,7 +1108,35 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
     record(gid, rec);
     gid1 = entry(max(lo - NB, 0), lo);
     uint64_t hit = 0;  // the staged splats that some pixel blends
-    if constexpr (PX > 1) {
+    if (odd) {  // splat by splat, the same operations in the same order
+#pragma unroll 1
+      for (int k = m - 1; k >= 0; --k) {
+        const uint32_t pos = L.pos[k];
+        const float4 a0 = L.s0[k], a1 = L.s1[k], a2 = L.s2[k];
+        const float ex = px - a0.x;
+        uint64_t some = 0;
+        float ey[PX], tg[PX], w[PX];
+#pragma unroll
+        for (int j = 0; j < PX; ++j) {
+          ey[j] = py[j] - a0.y;
+          const float Q = eval_q(px, py[j], a0.x, a0.y, a0.z, a0.w + a0.w, a1.x).Q;
+          uint64_t skip = __ballot(Q > a1.z);
+          if (~(skip | __ballot(Q <= a1.y)) != 0)
+            skip = __ballot(skips_f64(L.t[k], px, py[j], a0.x, a0.y, a0.z, a0.w, a1.x));
+          const uint64_t act = __ballot(pos < nc[j]) & ~skip;
+          some |= act;
+          tg[j] = w[j] = 0.f;
+          if (__builtin_amdgcn_inverse_ballot_w64(act))
+            bwd_pixel<DEPTH>(gauss(Q), a1.w, a2, dC0[j], dC1[j], dC2[j], dD[j], T[j], U[j], tg[j],
+                             w[j]);
+        }
+        if (some == 0) continue;
+        hit |= 1ull << k;
+        float m0, m1, m2, c[4];
+        bwd_lane_sums<PX, DEPTH>(tg, w, ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
+        bwd_reduce<DEPTH>(L.red, k, lane, a0, a1.x, a1.w, ex, m0, m1, m2, c);
+      }
+    } else if constexpr (PX > 1) {
       const uint32_t mine = lane < m ? L.cells[lane] : 0u;
       uint64_t has[PX];
 #pragma unroll
@@ -1348,9 +1430,10 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds<NW>& L, int x0, int y
 #pragma unroll
         for (int g = 0; g < G; ++g) {
           if (act[g] == 0) continue;  // uniform (the filler's t < 0 leaves it inactive)
-          const float Gs = gauss(
-              __builtin_amdgcn_inverse_ballot_w64(act[g]) ? Q[g] : __builtin_huge_valf());
-          const float4 p = bwd_pixel_shape<DEPTH>(Gs, a1[g].w, a2[g], e0, e1, e2, e3);
+          const bool on = __builtin_amdgcn_inverse_ballot_w64(act[g]);
+          float4 p = bwd_pixel_shape<DEPTH>(gauss(Q[g]), a1[g].w, a2[g], e0, e1, e2, e3);
+          // the other pixels pass unchanged, whatever the splat's values
+          p = make_float4(on ? p.x : 0.f, on ? p.y : 1.f, on ? p.z : 0.f, on ? p.w : 0.f);
           if constexpr (NW == 8) {
             L.px[k[g] - b0][cell][lane] = p;
           } else {
