@@ -390,13 +390,16 @@ __global__ void __launch_bounds__(kFwdThreads) k_decode_fwd(DecIn in, float* __r
     for (int t = 0; t < kOutTiles; ++t) {
       const int r = out_row(t, m);
       const uint16_t* wr = sW2 + (r >= 0 ? r : kOut) * kWS + 8 * kq;
+      const bf16x8 wv = lds8(wr);
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      if (t < 3) {  // row 4 i of the tile: opacity (head 0); the others: colour (head 1)
-        const uint16_t* zr = sW2 + kOut * kWS;
-        acc = mfma(lds8((m & 3) == 0 ? wr : zr), hid[0], acc);
-        acc = mfma(lds8((m & 3) == 0 ? zr : wr), hid[1], acc);
+      if (t < 3) {
+        // row 4 i of the tile: opacity (head 0); the others: colour (head 1). Each
+        // head has a sum of its own, so that an infinite hidden unit stays in it.
+        const f32x4 op = mfma(wv, hid[0], acc);
+        acc = mfma(wv, hid[1], acc);
+        acc[0] = op[0];
       } else {
-        acc = mfma(lds8(wr), hid[2], acc);
+        acc = mfma(wv, hid[2], acc);
       }
       const float4 bb = *reinterpret_cast<const float4*>(sB2 + 16 * t + 4 * kq);
       const float y0 = acc[0] + bb.x, y1 = acc[1] + bb.y, y2 = acc[2] + bb.z,
