@@ -1053,6 +1053,7 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
 #pragma unroll
   for (int d = 1; d < kWave; d <<= 1) most = max(most, (uint32_t)__shfl_xor((int)most, d, kWave));
   most = __builtin_amdgcn_readfirstlane(most);
+  if (most == 0) return;  // nothing blended: no record is read
   if (lane == 0) {  // the filler: t < 0 skips it
     L.s0[NB] = make_float4(0.f, 0.f, 1.f, 0.f);
     L.s1[NB] = make_float4(1.f, -1.f, -1.f, 0.f);
