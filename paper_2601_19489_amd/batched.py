@@ -192,8 +192,10 @@ class TrainStep:
 def autotune(make_step, tiles=(8, 16, 32), px=(1, 2, 4), persist=(8, 12, 16),
              fwd_batch=(64, 128, 256), bwd_batch=(32, 64, 128), warmup=2, iters=5, log=None):
     """Pick tile size, pixels per lane (forward, backward), persistent
-    workgroups per CU and the splats per LDS batch (forward batch, backward
-    bucket) by timing the batched step, one knob at a time.
+    workgroups per CU and the forward's splats per LDS batch by timing the
+    batched step, one knob at a time. bwd_batch is accepted and not searched:
+    the backward stages 64 list entries whatever the knob says, so a timing
+    could only pick a value by its noise.
 
     make_step(tile) returns a ready TrainStep for that tile size. Returns
     (best config dict, list of (config, ms per step)). The knobs do not
@@ -249,13 +251,12 @@ def autotune(make_step, tiles=(8, 16, 32), px=(1, 2, 4), persist=(8, 12, 16),
         ms = measure(best_tile, c)
         if ms < best_ms:
             best_ms, cfg = ms, c
-    for knob, values in (('fwd_batch', fwd_batch), ('bwd_batch', bwd_batch)):
-        for v in values:
-            if v == cfg[knob]:
-                continue
-            c = dict(cfg, **{knob: v})
-            ms = measure(best_tile, c)
-            if ms < best_ms:
-                best_ms, cfg = ms, c
+    for v in fwd_batch:
+        if v == cfg['fwd_batch']:
+            continue
+        c = dict(cfg, fwd_batch=v)
+        ms = measure(best_tile, c)
+        if ms < best_ms:
+            best_ms, cfg = ms, c
     _lib.gs_set_tuning(**cfg)
     return dict(tile=best_tile, **cfg), table
