@@ -121,16 +121,15 @@ __device__ __forceinline__ uint32_t cells_reached(float x0, float y0, float4 r0,
   return m;
 }
 
-// A splat whose colour, depth or opacity is not finite (or so large that their
-// sum is not) has to leave the pixels that do not blend it as they are, which a
-// weight of 0 does not. A wavefront whose batch of the list holds such a splat
+// A splat whose colour or depth is not finite (or so large that their sum is
+// not) has to leave the pixels that do not blend it as they are, which a weight
+// of 0 does not. A wavefront whose batch of the list holds such a splat
 // walks that batch splat by splat, under the mask of the pixels that blend it.
 // (The mask in the ordinary walk costs the forward 2 to 15%, a branch around
 // the odd splats of a group 1 to 12%, a walk of its own nothing.)
 constexpr uint32_t kOddSplat = 1u << 31;  // among the cells' bits
 __device__ __forceinline__ bool odd_splat(float4 r1, float4 r2) {  // (c, t, o, z), (r, g, b, -)
-  return !(fabsf(r2.x) + fabsf(r2.y) + fabsf(r2.z) + fabsf(r1.w) + fabsf(r1.z) <
-           __builtin_huge_valf());
+  return !(fabsf(r2.x) + fabsf(r2.y) + fabsf(r2.z) + fabsf(r1.w) < __builtin_huge_valf());
 }
 
 // 2 x + (the lane's bit of m), one instruction.
@@ -919,7 +918,7 @@ __device__ __forceinline__ void bwd_pixel_blend(float4 p, float& T, float& U, fl
   const float Tb = T * p.y;  // transmittance in front of this splat
   w = p.x * Tb;
   const float dal = p.y * fmaf(T, p.z, -U);
-  tg = p.w > 0.f ? dal * p.w : 0.f;  // none through the clamp or with G = 0 (U may be NaN)
+  tg = p.w >= 0.f ? dal * p.w : 0.f;  // no gradient through the clamp
   U = fmaf(w, p.z, U);
   T = Tb;
 }
@@ -1079,6 +1078,7 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
   float4 rec[3];
   record(gid, rec);
   uint32_t gid1 = entry(max(lo - NB, 0), lo);
+  bool odd = false;  // from the first odd splat on: U may not be finite behind it
   while (hi > 0) {
     // stage: the entries that reach the region, compacted in list order
     uint32_t cells = 0;  // an id past n (never for a correct list) reaches nothing
@@ -1089,7 +1089,7 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
                                         [](int) { return 0; }, [](int i) { return CH * i; });
     }
     const uint64_t reach = __ballot(cells != 0);
-    const bool odd = __ballot(cells != 0 && odd_splat(rec[1], rec[2])) != 0;
+    odd = odd || __ballot(cells != 0 && odd_splat(rec[1], rec[2])) != 0;
     const int m = (int)__popcll(reach);
     if (cells != 0) {
       const int k = (int)__builtin_amdgcn_mbcnt_hi(
@@ -1432,9 +1432,12 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds<NW>& L, int x0, int y
         for (int g = 0; g < G; ++g) {
           if (act[g] == 0) continue;  // uniform (the filler's t < 0 leaves it inactive)
           const bool on = __builtin_amdgcn_inverse_ballot_w64(act[g]);
-          float4 p = bwd_pixel_shape<DEPTH>(gauss(Q[g]), a1[g].w, a2[g], e0, e1, e2, e3);
-          // the other pixels pass unchanged, whatever the splat's values
-          p = make_float4(on ? p.x : 0.f, on ? p.y : 1.f, on ? p.z : 0.f, on ? p.w : 0.f);
+          const float Gs = gauss(on ? Q[g] : __builtin_huge_valf());
+          float4 p = bwd_pixel_shape<DEPTH>(Gs, a1[g].w, a2[g], e0, e1, e2, e3);
+          // the other pixels pass unchanged (alpha is 0), whatever the splat's
+          // colour and their own U
+          p.z = on ? p.z : 0.f;
+          p.w = on ? p.w : -1.f;
           if constexpr (NW == 8) {
             L.px[k[g] - b0][cell][lane] = p;
           } else {
