@@ -219,9 +219,9 @@ __device__ __forceinline__ void snug_rows(const Snug& s, int tx, int tile, int t
 // Gaussians they hold as one flattened list, 64 columns per round, so a
 // Gaussian spanning a hundred columns does not stall the other 63 lanes.
 // f(owner_lane, tx, ty0, ty1, first) runs once per column (ty0 > ty1: the
-// column's rows fall outside the grid), by all lanes together. Every thread of the workgroup must call it
-// (it synchronises the workgroup); `lds` is 64 entries of this wavefront's
-// scratch, `mark` 64 words of it.
+// column's rows fall outside the grid), by all lanes together. Every thread of
+// the workgroup must call it (it synchronises the workgroup); `lds` is 64
+// entries of this wavefront's scratch, `mark` 64 words of it.
 struct SnugLds {
   Snug s;
   int tx0;

@@ -145,7 +145,8 @@ __device__ void stage_weights(const float* __restrict__ w1, const float* __restr
   for (int q = 0; q < kP2; ++q) {
     const int e = tid + q * kBwdThreads, r = e / kHid;
     const int hd = r < head_row(1) ? 0 : r < head_row(2) ? 1 : 2;
-    if (e < kOut * kHid) s[kStageW2 + (head_base(hd) + r - head_row(hd)) * kHid + e % kHid] = f2bf(v2[q]);
+    if (e < kOut * kHid)
+      s[kStageW2 + (head_base(hd) + r - head_row(hd)) * kHid + e % kHid] = f2bf(v2[q]);
   }
   for (int e = tid; e < kHidAll * (64 - kIn); e += kBwdThreads)
     s[e / (64 - kIn) * 64 + kIn + e % (64 - kIn)] = 0;
@@ -418,7 +419,8 @@ __global__ void __launch_bounds__(kFwdThreads) k_decode_fwd(DecIn in, float* __r
         scales[N + g] = ss[1] * sigm(y1);
         scales[2 * N + g] = ss[2] * sigm(y2);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) means[d * N + g] = pos[d] + off[min(max(t - 3, 0), 2)][d] * so[d];
+        for (int d = 0; d < 3; ++d)
+          means[d * N + g] = pos[d] + off[min(max(t - 3, 0), 2)][d] * so[d];
       } else if (slot >= 22) {
         const int64_t g = (slot - 22) * A + ai;
         const float inv = 1.f / sqrtf(y0 * y0 + y1 * y1 + y2 * y2 + y3 * y3);
@@ -442,8 +444,8 @@ struct DecGrad {
 // wavefronts: sX (BF16 inputs), sH (BF16 hidden units), sY (FP32 y + b2 in
 // padded columns), divided as above. Ends with a barrier.
 __device__ void tile_forward(const DecIn& in, const Bias& B, int64_t a0, int tid, int h,
-                             const FwdWQuarter& W, uint16_t* sX, uint16_t* sH, float* sY, uint16_t* sXT,
-                             uint16_t* sHT) {
+                             const FwdWQuarter& W, uint16_t* sX, uint16_t* sH, float* sY,
+                             uint16_t* sXT, uint16_t* sHT) {
   const int64_t A = in.A;
   {
     constexpr int kPer = kFeat * kTile / kBwdThreads;  // 2

@@ -126,7 +126,7 @@ __device__ __forceinline__ uint32_t cells_reached(float x0, float y0, float4 r0,
 // of 0 does not. A wavefront whose batch of the list holds such a splat
 // walks that batch splat by splat, under the mask of the pixels that blend it.
 // (The mask in the ordinary walk costs the forward 2 to 15%, a branch around
-// the odd splats of a group 1 to 12%, a walk of its own nothing.)
+// the odd splats of a group 1 to 12%, a walk of its own under 1%.)
 constexpr uint32_t kOddSplat = 1u << 31;  // among the cells' bits
 __device__ __forceinline__ bool odd_splat(float4 r1, float4 r2) {  // (c, t, o, z), (r, g, b, -)
   return !(fabsf(r2.x) + fabsf(r2.y) + fabsf(r2.z) + fabsf(r1.w) < __builtin_huge_valf());
@@ -147,7 +147,8 @@ constexpr int kFwdGroup = 4;    // splats a wavefront evaluates together (fwd_ti
 // nowhere: it fills up a wavefront's last group.
 template <int NB, int NTH>
 struct FwdLdsT {
-  float4 s0[NB + 1], s1[NB + 1], s2[NB + 1];  // (u, v, a, 2 b), (c, t - band, t + band, o), (r, g, b, z)
+  // (u, v, a, 2 b), (c, t - band, t + band, o), (r, g, b, z)
+  float4 s0[NB + 1], s1[NB + 1], s2[NB + 1];
   float t[NB + 1];
   uint32_t cells[NB + 1];
   alignas(16) uint32_t list[NTH / kWave][NB + kFwdGroup];
@@ -158,7 +159,9 @@ struct FwdLdsT {
 // w PX .. w PX + PX - 1.
 struct FwdCells {
   __host__ __device__ static constexpr int x(int i) { return 8 * ((i & 1) | ((i >> 1) & 2)); }
-  __host__ __device__ static constexpr int y(int i) { return 8 * (((i >> 1) & 1) | ((i >> 2) & 2)); }
+  __host__ __device__ static constexpr int y(int i) {
+    return 8 * (((i >> 1) & 1) | ((i >> 2) & 2));
+  }
 };
 
 // Stage the record of Gaussian g (g >= n: a splat that blends nowhere, since
@@ -875,7 +878,8 @@ constexpr int kBwdGroup = 2;   // splats evaluated together with one pixel per l
 // The staged splats that reach the region, in list order. Entry kBwdBatch holds
 // a splat that blends nowhere: it fills up the last group.
 struct BwdLds {
-  float4 s0[kBwdBatch + 1], s1[kBwdBatch + 1], s2[kBwdBatch + 1];  // (u, v, a, b), (c, t - band, t + band, o), (r, g, b, z)
+  // (u, v, a, b), (c, t - band, t + band, o), (r, g, b, z)
+  float4 s0[kBwdBatch + 1], s1[kBwdBatch + 1], s2[kBwdBatch + 1];
   float t[kBwdBatch + 1];
   uint32_t sid[kBwdBatch + 1], pos[kBwdBatch + 1], cells[kBwdBatch + 1];
   float red[GS_GRAD2D_COMPONENTS][kBwdBatch + 1];  // the region's sums per splat
@@ -1000,14 +1004,19 @@ __device__ __forceinline__ void bwd_reduce(float (&red)[GS_GRAD2D_COMPONENTS][N]
 // the wavefront included), the walk of the longest lists where splats are
 // small. So a wavefront stages only the splats that reach its region, reads a
 // list entry's record a batch ahead, and skips the cells that a splat does
-// not reach; splats that reach all of them take the pixels of a lane side by
-// side; with one pixel per lane two splats are evaluated together, so that
-// only T and U pass from one to the next. With the long regions of
-// bwd_region_coop, against one wavefront per tile walking the whole list:
-// 873 -> 335 us (300k Gaussians of about their spacing's size, 1600x1066),
-// 1476 -> 525 us (1M children of 100k anchors), 272 -> 73 us (1000 Gaussians,
-// 64x64), 583 -> 558 us (1M Gaussians of the surface scene, 1600x1066). With
-// 96 registers for five wavefronts a SIMD (a few spilled): 581 us for the last.
+// not reach; splats that reach more than half of them take the pixels of a lane
+// side by side (from two of four cells on, three, or all four only: 806, 808
+// and 825 us at 300k Gaussians of about their spacing's size without a tile
+// order, 650, 646 and 647 us for the surface scene); with one pixel per lane two
+// splats are evaluated together, so that only T and U pass from one to the next.
+// With the long regions of bwd_region_coop, against one wavefront per tile
+// walking the whole list: 873 -> 335 us (300k Gaussians of about their spacing's
+// size, 1600x1066), 1476 -> 525 us (1M children of 100k anchors), 272 -> 73 us
+// (1000 Gaussians, 64x64), 583 -> 558 us (1M Gaussians of the surface scene,
+// 1600x1066). With 96 registers for five wavefronts a SIMD (a few spilled): 581
+// us for the last. Fewer pixels per lane mean more regions to a tile, each with
+// its own adds: with one (16-pixel tiles) 626 -> 270 us on the first scene, but
+// 1280 -> 1450 us on the last.
 template <int TILE, int PX, bool DEPTH>
 __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t start,
                                            const float* __restrict__ splats,
@@ -1142,7 +1151,7 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
       uint64_t has[PX];
 #pragma unroll
       for (int j = 0; j < PX; ++j) has[j] = __ballot((mine >> j) & 1u);
-      const uint64_t all = __ballot(__builtin_popcount(mine) > PX / 2);
+      const uint64_t most_cells = __ballot(__builtin_popcount(mine) > PX / 2);
       for (int k = m - 1; k >= 0; --k) {
         const uint32_t pos = L.pos[k];  // position in the tile list
         const float4 a0 = L.s0[k], a1 = L.s1[k], a2 = L.s2[k];
@@ -1151,14 +1160,15 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
         const float aex = a0.z * ex;
         uint64_t act[PX], some = 0, near = 0;
         float Q[PX], ey[PX], tg[PX], w[PX];
-        // every: all cells are reached, and the pixels of a lane go side by
-        // side; otherwise the reached cells, one after the other
-        const auto shapes = [&](auto every) {
+        // beside: more than half of the cells are reached, and the pixels of a
+        // lane go side by side (those of a cell that is not reached are skipped
+        // by Q > t); otherwise the reached cells, one after the other
+        const auto shapes = [&](auto beside) {
 #pragma unroll
           for (int j = 0; j < PX; ++j) {
             act[j] = 0;
             ey[j] = py[j] - a0.y;
-            if (!every.value && !((has[j] >> k) & 1ull)) continue;  // uniform
+            if (!beside.value && !((has[j] >> k) & 1ull)) continue;  // uniform
             const float t1 = a1.x * ey[j];
             const float td = t1 * ey[j];
             Q[j] = fmaf(ex, fmaf(b2, ey[j], aex), td);  // same value as eval_q
@@ -1168,11 +1178,11 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
             some |= act[j];
           }
         };
-        const auto terms = [&](auto every) {
+        const auto terms = [&](auto beside) {
 #pragma unroll
           for (int j = 0; j < PX; ++j) {
             tg[j] = w[j] = 0.f;
-            if (!every.value && act[j] == 0) continue;  // uniform
+            if (!beside.value && act[j] == 0) continue;  // uniform
             // an inactive pixel runs the same arithmetic with alpha = 0: no change
             const float G = gauss(
                 __builtin_amdgcn_inverse_ballot_w64(act[j]) ? Q[j] : __builtin_huge_valf());
@@ -1180,8 +1190,8 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
                              w[j]);
           }
         };
-        const bool every = (all >> k) & 1ull;
-        if (every) shapes(std::true_type{}); else shapes(std::false_type{});
+        const bool beside = (most_cells >> k) & 1ull;
+        if (beside) shapes(std::true_type{}); else shapes(std::false_type{});
         if (near != 0) {  // a few splats in a thousand: the FP64 decision
           asm volatile("");  // not to be computed ahead of the branch
           some = 0;
@@ -1195,7 +1205,7 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
         if (some == 0) continue;
         hit |= 1ull << k;
         float m0, m1, m2, c[4];
-        if (every) {
+        if (beside) {
           terms(std::true_type{});
           bwd_lane_sums<PX, DEPTH>(tg, w, ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
         } else {
@@ -1453,7 +1463,8 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds<NW>& L, int x0, int y
       uint32_t hits[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        hits[j] = __builtin_amdgcn_readfirstlane(L.hit[par][j] | (NW == 8 ? L.hit[par][NW - 4 + j] : 0u));
+        hits[j] = __builtin_amdgcn_readfirstlane(
+            L.hit[par][j] | (NW == 8 ? L.hit[par][NW - 4 + j] : 0u));
       if (NW == 8 && wv < 4) {  // T and U through the cell's entries, last first
         uint32_t left = wv == 0 ? hits[0] : wv == 1 ? hits[1] : wv == 2 ? hits[2] : hits[3];
         constexpr int R = 4;  // entries read together
@@ -1550,6 +1561,11 @@ union BwdShared<NW, false> {
 // against 8: 90 and 73 us (16 regions), 153 and 122 us (144), 101 and 92 us
 // (950), 274 and 257 us (3600); 328 and 360 us, 527 and 746 us (6700 regions,
 // 300k Gaussians of about their spacing's size and 1M children of anchors).
+// The line lies somewhere between those two sizes, and it counts empty regions
+// too: where most of a large view is empty, 8 would be faster (100k Gaussians
+// in 65 tiles of a 1920x1080 view, 8160 regions: 1710 us with 4, 1452 with 8,
+// 5249 with one wavefront to a tile), but the launch is chosen before the lists
+// are known.
 constexpr int64_t kBwdFewRegions = 4096;
 template <int TILE, int PX>
 constexpr bool bwd_can_split() { return PX == 4 && TILE >= 16; }
@@ -1574,8 +1590,9 @@ __device__ __forceinline__ void bwd_one(Shared& L, int tile, int part,
   const int x0 = tile / tiles_y * TILE + bwd_region_x<TILE, PX>(part);
   const int y0 = tile % tiles_y * TILE + bwd_region_y<TILE, PX>(part);
   if constexpr (!std::is_same<Shared, BwdLds>::value)
-    bwd_region_coop<Shared::kWaves, DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1, bg2, T_final,
-                           n_contrib, dL_dimage, dL_ddepth, grad2d, n);
+    bwd_region_coop<Shared::kWaves, DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1,
+                                           bg2, T_final, n_contrib, dL_dimage, dL_ddepth, grad2d,
+                                           n);
   else
     bwd_region<TILE, PX, DEPTH>(L, x0, y0, ranges[tile], splats, vals, W, H, bg0, bg1, bg2,
                                 T_final, n_contrib, dL_dimage, dL_ddepth, grad2d, n);
@@ -1826,10 +1843,8 @@ __device__ __forceinline__ int view_of(const ViewSet& vs, int it) {
 
 template <int TILE, int PX, int NB>
 __global__ void __launch_bounds__(TILE* TILE / PX)
-__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched(ViewSet vs, int64_t n,
-                                                                         float bg0, float bg1,
-                                                                         float bg2,
-                                                                         uint32_t* queue) {
+__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched(
+    ViewSet vs, int64_t n, float bg0, float bg1, float bg2, uint32_t* queue) {
   __shared__ FwdLdsT<NB, TILE * TILE / PX> L;
   __shared__ int s_item;
   for (int it; (it = next_item(queue, vs.total, &s_item)) >= 0;) {
@@ -1844,10 +1859,8 @@ __attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched(V
 // per view); each view's vals receives the list positions it stages.
 template <int TILE, int PX, int NB>
 __global__ void __launch_bounds__(TILE* TILE / PX)
-__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched_def(ViewSet vs, int64_t n,
-                                                                             float bg0, float bg1,
-                                                                             float bg2,
-                                                                             uint32_t* queue) {
+__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd_batched_def(
+    ViewSet vs, int64_t n, float bg0, float bg1, float bg2, uint32_t* queue) {
   __shared__ FwdLdsT<NB, TILE * TILE / PX> L;
   __shared__ DefLds<NB, TILE * TILE / PX> DL;
   __shared__ int s_item;

@@ -278,8 +278,8 @@ __global__ void __launch_bounds__(kSortThreads) k_radix_scatter(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t n_max,
     const uint32_t* __restrict__ n_dev, int shift, const uint32_t* __restrict__ hist,
-    const uint32_t* __restrict__ groups, const uint32_t* __restrict__ vals2_in, uint32_t* __restrict__ vals2_out, int bits,
-    int vals2_stride) {
+    const uint32_t* __restrict__ groups, const uint32_t* __restrict__ vals2_in,
+    uint32_t* __restrict__ vals2_out, int bits, int vals2_stride) {
   constexpr int NW = kSortThreads / kWave;
   constexpr int T = kSortThreads * ITEMS;
   __shared__ uint32_t cnt[NW][kRadixBins];
