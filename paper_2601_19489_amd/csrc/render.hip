@@ -603,16 +603,17 @@ __device__ __forceinline__ void fwd_tile(FwdLdsT<NB, TILE * TILE / PX>& L, int t
 // tiles: 299 against 300 us on the 1920x1080 view of the surface scene, 138
 // against 145 us at 300k Gaussians of about their spacing's size. 32-pixel
 // tiles have 16 wavefronts to a workgroup: two of them need 8 (372 against 455
-// us with one). With two pixels per lane the registers decide; with four, 128
-// registers (142 with the walk of odd splats, at 32-pixel tiles: 355 against
-// 339 us on the surface scene).
-constexpr int fwd_waves(int tile, int px) {
-  return px == 4 ? 4 : px == 2 ? 1 : tile == 32 ? 8 : 7;
+// us with one). With several pixels per lane the registers of the ordinary walk
+// decide, and the walk of odd splats has to do with as many (32-pixel tiles, four
+// pixels, lists given: 3 and 142 registers 355 us, 4 and 128 339 us on the surface
+// scene).
+constexpr int fwd_waves(int tile, int px, bool lists = false) {
+  return px == 4 ? (lists ? 4 : 3) : px == 2 ? 1 : tile == 32 ? 8 : 7;
 }
 
 template <int TILE, int PX>
 __global__ void __launch_bounds__(TILE* TILE / PX)
-__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX)))) k_render_fwd(
+__attribute__((amdgpu_waves_per_eu(fwd_waves(TILE, PX, true)))) k_render_fwd(
     const float* __restrict__ splats, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ ranges, int64_t n, int W, int H, int tiles_y, float bg0,
     float bg1, float bg2, float* __restrict__ image, float* __restrict__ depth,
@@ -1118,40 +1119,12 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
     record(gid, rec);
     gid1 = entry(max(lo - NB, 0), lo);
     uint64_t hit = 0;  // the staged splats that some pixel blends
-    if (odd) {  // splat by splat, the same operations in the same order
-#pragma unroll 1
-      for (int k = m - 1; k >= 0; --k) {
-        const uint32_t pos = L.pos[k];
-        const float4 a0 = L.s0[k], a1 = L.s1[k], a2 = L.s2[k];
-        const float ex = px - a0.x;
-        uint64_t some = 0;
-        float ey[PX], tg[PX], w[PX];
-#pragma unroll
-        for (int j = 0; j < PX; ++j) {
-          ey[j] = py[j] - a0.y;
-          const float Q = eval_q(px, py[j], a0.x, a0.y, a0.z, a0.w + a0.w, a1.x).Q;
-          uint64_t skip = __ballot(Q > a1.z);
-          if (~(skip | __ballot(Q <= a1.y)) != 0)
-            skip = __ballot(skips_f64(L.t[k], px, py[j], a0.x, a0.y, a0.z, a0.w, a1.x));
-          const uint64_t act = __ballot(pos < nc[j]) & ~skip;
-          some |= act;
-          tg[j] = w[j] = 0.f;
-          if (__builtin_amdgcn_inverse_ballot_w64(act))
-            bwd_pixel<DEPTH>(gauss(Q), a1.w, a2, dC0[j], dC1[j], dC2[j], dD[j], T[j], U[j], tg[j],
-                             w[j]);
-        }
-        if (some == 0) continue;
-        hit |= 1ull << k;
-        float m0, m1, m2, c[4];
-        bwd_lane_sums<PX, DEPTH>(tg, w, ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
-        bwd_reduce<DEPTH>(L.red, k, lane, a0, a1.x, a1.w, ex, m0, m1, m2, c);
-      }
-    } else if constexpr (PX > 1) {
+    if constexpr (PX > 1) {
       const uint32_t mine = lane < m ? L.cells[lane] : 0u;
       uint64_t has[PX];
 #pragma unroll
       for (int j = 0; j < PX; ++j) has[j] = __ballot((mine >> j) & 1u);
-      const uint64_t most_cells = __ballot(__builtin_popcount(mine) > PX / 2);
+      const uint64_t most_cells = odd ? 0ull : __ballot(__builtin_popcount(mine) > PX / 2);
       for (int k = m - 1; k >= 0; --k) {
         const uint32_t pos = L.pos[k];  // position in the tile list
         const float4 a0 = L.s0[k], a1 = L.s1[k], a2 = L.s2[k];
@@ -1162,7 +1135,8 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
         float Q[PX], ey[PX], tg[PX], w[PX];
         // beside: more than half of the cells are reached, and the pixels of a
         // lane go side by side (those of a cell that is not reached are skipped
-        // by Q > t); otherwise the reached cells, one after the other
+        // by Q > t); otherwise, and from the first odd splat on, the reached
+        // cells one after the other, under the mask of the pixels that blend
         const auto shapes = [&](auto beside) {
 #pragma unroll
           for (int j = 0; j < PX; ++j) {
@@ -1182,10 +1156,17 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
 #pragma unroll
           for (int j = 0; j < PX; ++j) {
             tg[j] = w[j] = 0.f;
-            if (!beside.value && act[j] == 0) continue;  // uniform
+            const bool on = __builtin_amdgcn_inverse_ballot_w64(act[j]);
+            if (!beside.value) {
+              if (on) {
+                asm volatile("");  // masked, not selected
+                bwd_pixel<DEPTH>(gauss(Q[j]), a1.w, a2, dC0[j], dC1[j], dC2[j], dD[j], T[j], U[j],
+                                 tg[j], w[j]);
+              }
+              continue;
+            }
             // an inactive pixel runs the same arithmetic with alpha = 0: no change
-            const float G = gauss(
-                __builtin_amdgcn_inverse_ballot_w64(act[j]) ? Q[j] : __builtin_huge_valf());
+            const float G = gauss(on ? Q[j] : __builtin_huge_valf());
             bwd_pixel<DEPTH>(G, a1.w, a2, dC0[j], dC1[j], dC2[j], dD[j], T[j], U[j], tg[j],
                              w[j]);
           }
@@ -1212,6 +1193,25 @@ __device__ __forceinline__ void bwd_region(BwdLds& L, int x0, int y0, uint32_t s
           terms(std::false_type{});
           bwd_lane_sums<PX, DEPTH>(tg, w, ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
         }
+        bwd_reduce<DEPTH>(L.red, k, lane, a0, a1.x, a1.w, ex, m0, m1, m2, c);
+      }
+    } else if (odd) {  // splat by splat, the same operations in the same order
+#pragma unroll 1
+      for (int k = m - 1; k >= 0; --k) {
+        const uint32_t pos = L.pos[k];
+        const float4 a0 = L.s0[k], a1 = L.s1[k], a2 = L.s2[k];
+        const float ex = px - a0.x, ey = py[0] - a0.y;
+        const float Q = eval_q(px, py[0], a0.x, a0.y, a0.z, a0.w + a0.w, a1.x).Q;
+        uint64_t skip = __ballot(Q > a1.z);
+        if (~(skip | __ballot(Q <= a1.y)) != 0)
+          skip = __ballot(skips_f64(L.t[k], px, py[0], a0.x, a0.y, a0.z, a0.w, a1.x));
+        const uint64_t act = __ballot(pos < nc[0]) & ~skip;
+        if (act == 0) continue;
+        hit |= 1ull << k;
+        float tg = 0.f, w = 0.f, m0, m1, m2, c[4];
+        if (__builtin_amdgcn_inverse_ballot_w64(act))
+          bwd_pixel<DEPTH>(gauss(Q), a1.w, a2, dC0[0], dC1[0], dC2[0], dD[0], T[0], U[0], tg, w);
+        bwd_lane_sums<1, DEPTH>(&tg, &w, &ey, dC0, dC1, dC2, dD, m0, m1, m2, c);
         bwd_reduce<DEPTH>(L.red, k, lane, a0, a1.x, a1.w, ex, m0, m1, m2, c);
       }
     } else {
@@ -1600,8 +1600,10 @@ __device__ __forceinline__ void bwd_one(Shared& L, int tile, int part,
 
 // order, work: the tiles heaviest first and each tile's largest n_contrib
 // (null: tile-id order, one wavefront per region).
+// Two pixels per lane without depth: 80 registers, six wavefronts per SIMD.
 template <int TILE, int PX, bool DEPTH, int NW>
-__global__ void __launch_bounds__(NW* kWave) k_render_bwd(
+__global__ void __launch_bounds__(NW* kWave)
+__attribute__((amdgpu_waves_per_eu(PX == 2 && !DEPTH ? 6 : 1))) k_render_bwd(
     const float* __restrict__ splats, const uint32_t* __restrict__ vals,
     const uint32_t* __restrict__ ranges, int W, int H, int nt, int tiles_y, float bg0, float bg1,
     float bg2, const float* __restrict__ T_final, const uint32_t* __restrict__ n_contrib,
