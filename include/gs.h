@@ -163,7 +163,8 @@ gs_status gs_bin_sort_deferred(const float* splats, const uint32_t* depth_keys,
  * skips a splat where Q > t (alpha < 1/255), stops before the splat that
  * would take the transmittance below 1e-4f, and blends colour and centroid
  * depth (Sec. 3.1 uses the centroid depth). The clamp and the stop
- * threshold are the FP32 constants; alpha and the transmittance are FP32.
+ * threshold are the FP32 constants; alpha and the transmittance are FP32. A
+ * colour or depth that is not finite reaches the pixels that blend its splat.
  *   splats, n    records of the n Gaussians (gs_preprocess); list entries
  *                >= n are treated as absent
  *   vals, ranges sorted lists from gs_bin_sort
