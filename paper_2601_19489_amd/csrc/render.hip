@@ -1390,9 +1390,10 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds<NW>& L, int x0, int y
     if (wv == turn % NW) {
       uint32_t cells = 0;  // an id past n (never for a correct list) reaches nothing
       if ((int64_t)gid < n) {
-        const float band = skip_band(rec[0].z, rec[0].w, rec[1].x, rec[1].y);
+        float band = skip_band(rec[0].z, rec[0].w, rec[1].x, rec[1].y);
         cells = cells_reached<16, 4, 4>((float)x0, (float)y0, rec[0], rec[1].x, rec[1].y, band,
                                         [](int) { return 0; }, [](int i) { return 4 * i; });
+        if (odd_splat(rec[1], rec[2])) band = __builtin_huge_valf();  // to the FP64 decision
         L.s0[lane] = rec[0];
         L.s1[lane] = make_float4(rec[1].x, rec[1].y - band, rec[1].y + band, rec[1].z);
         L.s2[lane] = make_float4(rec[2].x, rec[2].y, rec[2].z, rec[1].w);
@@ -1433,10 +1434,15 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds<NW>& L, int x0, int y
         if (near != 0) {  // a few groups in a thousand: the FP64 decision
           asm volatile("");  // not to be computed ahead of the branch
 #pragma unroll
-          for (int g = 0; g < G; ++g)
-            act[g] = __ballot((uint32_t)(lo + k[g]) < nc &&
-                              !skips_f64(L.t[k[g]], px, my_py, a0[g].x, a0[g].y, a0[g].z,
-                                         a0[g].w, a1[g].x));
+          for (int g = 0; g < G; ++g) {
+            const bool on = (uint32_t)(lo + k[g]) < nc &&
+                            !skips_f64(L.t[k[g]], px, my_py, a0[g].x, a0[g].y, a0[g].z, a0[g].w,
+                                       a1[g].x);
+            act[g] = __ballot(on);
+            // the other pixels pass unchanged whatever the splat's colour
+            a2[g] = make_float4(on ? a2[g].x : 0.f, on ? a2[g].y : 0.f, on ? a2[g].z : 0.f,
+                                on ? a2[g].w : 0.f);
+          }
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
@@ -1444,10 +1450,7 @@ __device__ __forceinline__ void bwd_region_coop(BwdCoopLds<NW>& L, int x0, int y
           const bool on = __builtin_amdgcn_inverse_ballot_w64(act[g]);
           const float Gs = gauss(on ? Q[g] : __builtin_huge_valf());
           float4 p = bwd_pixel_shape<DEPTH>(Gs, a1[g].w, a2[g], e0, e1, e2, e3);
-          // the other pixels pass unchanged (alpha is 0), whatever the splat's
-          // colour and their own U
-          p.z = on ? p.z : 0.f;
-          p.w = on ? p.w : -1.f;
+          p.w = on ? p.w : -1.f;  // no gradient from the others, whatever their U
           if constexpr (NW == 8) {
             L.px[k[g] - b0][cell][lane] = p;
           } else {
